@@ -20,7 +20,7 @@ SANITIZE = os.environ.get("AGNES_SANITIZE", "")
 LIB = os.path.join(HERE, "libagnes.san.so" if SANITIZE else "libagnes.so")
 if SANITIZE:
     BUILD = os.path.join(HERE, "_build_san")
-SOURCES = ["prims.hip", "store.hip", "pipeline.hip", "bucket.hip", "sage.hip", "api.hip"]
+SOURCES = ["prims.hip", "store.hip", "pipeline.hip", "bucket.hip", "bitmap.hip", "sage.hip", "api.hip"]
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HIPCC = os.environ.get("HIPCC", os.path.join(ROCM, "bin", "hipcc"))
 ARCH = "gfx950"

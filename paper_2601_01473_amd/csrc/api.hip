@@ -147,7 +147,7 @@ static void release_batch(Batch* b) {
     if (b && b->magic == kBatchMagic) {
         if (b->state == kSampled || b->state == kGathering) {
             // let enqueued work finish before the memory goes away
-            if (b->state == kSampled && b->sampled_at) (void)hipEventSynchronize(b->sampled_at);
+            if (b->state == kSampled && b->listed_at) (void)hipEventSynchronize(b->listed_at);
             if (b->state == kGathering && b->gathered_at) (void)hipEventSynchronize(b->gathered_at);
         }
         if (b->sage_pending && b->sage_done) (void)hipEventSynchronize(b->sage_done);

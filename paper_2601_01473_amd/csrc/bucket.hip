@@ -31,6 +31,7 @@
 #include <cstring>
 #include <vector>
 
+#include "bitmap.hpp"
 #include "bucket.hpp"
 #include "device.hpp"
 #include "runtime.hpp"
@@ -38,6 +39,95 @@
 namespace agnes {
 
 // ----------------------------------------------------------------- levels (host)
+
+// The bitmap path's list blocks and node ranges, cut where the running weight
+// (in-degree plus c, which follows the sampled neighbours) reaches an even
+// share: with pieces of equal length a skewed graph's low ids, and with them a
+// third of the work, would fall to one workgroup.  A list block has at most
+// kBmListNodes nodes and holds whole feature blocks, or a piece of one (where
+// one alone is too long or too heavy).  A range has at most 2^17 nodes (16 KiB of
+// bits), or more where that would make more than 128 ranges, and begins with a
+// list block.
+static void build_ranges(Store& s, const std::vector<uint32_t>& indeg, double c, double W, int64_t n) {
+    const double share = W / (double)std::max<int64_t>(1, std::min<int64_t>(16384, n / 16));
+    const int64_t rpb = s.rpb;
+    std::vector<int32_t> blk{0}, spans;
+    std::vector<double> bw;
+    {
+        double acc = 0.0, part = 0.0;                  // weight since the block's start, and since the feature block's
+        int64_t start = 0, fstart = 0;
+        size_t first = 0;                              // list block in which the feature block starts
+        auto close = [&](int64_t end, double weight) {
+            blk.push_back((int32_t)end);
+            bw.push_back(weight);
+            start = end;
+        };
+        for (int64_t u = 0; u < n; u++) {
+            const double wu = (double)indeg[(size_t)u] + c;
+            acc += wu;
+            part += wu;
+            const int64_t end = u + 1;
+            const bool fend = end - fstart == rpb || end == n;
+            if (!fend && (end - start >= kBmListNodes || acc >= 2.0 * share)) {
+                if (start < fstart) {                  // the whole feature blocks before this one
+                    close(fstart, acc - part);
+                    acc = part;
+                    first = bw.size();
+                }
+                if (end - start >= kBmListNodes || acc >= 2.0 * share) {
+                    close(end, acc);
+                    acc = 0.0;
+                }
+            }
+            if (!fend) continue;
+            if (start > fstart || acc >= share || end - start + rpb > kBmListNodes || end == n) {
+                if (start < end) {
+                    close(end, acc);
+                    acc = 0.0;
+                }
+            }
+            if (bw.size() > first + 1 && blk[first] == fstart) {
+                spans.push_back((int32_t)first);
+                spans.push_back((int32_t)bw.size());
+            }
+            fstart = end;
+            part = 0.0;
+            first = bw.size();
+        }
+    }
+    s.n_list_blocks = (int64_t)bw.size();
+    s.n_list_spans = (int)(spans.size() / 2);
+    s.list_spans.reserve(std::max<size_t>(1, spans.size()) * 4);
+    AGNES_CHECK_HIP(hipMemcpy(s.list_spans.ptr, spans.data(), spans.size() * 4, hipMemcpyHostToDevice));
+    int64_t cap = (int64_t)1 << 17;
+    while (cap * 64 <= n && cap < ((int64_t)1 << 19)) cap *= 2;
+    cap = n <= ((int64_t)1 << 25) ? std::min(cap, (int64_t)1 << 18) : cap;
+    std::vector<int32_t> all;
+    for (int q = 0; q < kRangeTables; q++) {
+        const double target = W / (double)(1 << q);
+        std::vector<int32_t> bound{0}, first{0};
+        double sum = 0.0;
+        for (size_t i = 0; i < bw.size(); i++) {
+            if (i > 0 && (sum >= 0.99 * target || blk[i + 1] - bound.back() > cap)) {
+                bound.push_back(blk[i]);
+                first.push_back((int32_t)i);
+                sum = 0.0;
+            }
+            sum += bw[i];
+        }
+        bound.push_back((int32_t)n);
+        first.push_back((int32_t)bw.size());
+        int longest = 0;
+        for (size_t i = 0; i + 1 < bound.size(); i++) longest = std::max(longest, bound[i + 1] - bound[i]);
+        s.range_tab[q] = Store::RangeTable{(int)all.size(), (int)bound.size() - 1, (longest + 255) / 256 * 256};
+        all.insert(all.end(), bound.begin(), bound.end());
+        all.insert(all.end(), first.begin(), first.end());
+    }
+    s.list_blocks.reserve(blk.size() * 4);
+    s.ranges.reserve(all.size() * 4);
+    AGNES_CHECK_HIP(hipMemcpy(s.list_blocks.ptr, blk.data(), blk.size() * 4, hipMemcpyHostToDevice));
+    AGNES_CHECK_HIP(hipMemcpy(s.ranges.ptr, all.data(), all.size() * 4, hipMemcpyHostToDevice));
+}
 
 void build_bucket_levels(Store& s, const int32_t* indices, int64_t n, int64_t e) {
     std::vector<uint32_t> indeg((size_t)n, 0u);
@@ -81,6 +171,7 @@ void build_bucket_levels(Store& s, const int32_t* indices, int64_t n, int64_t e)
             w0.push_back(acc);
         }
     }
+    build_ranges(s, indeg, c, W, n);
     // coarser levels: neighbouring buckets merged up to twice the previous
     // budget; a bucket above the new budget stays alone (nested by construction)
     std::vector<std::vector<int32_t>> lev{b0};

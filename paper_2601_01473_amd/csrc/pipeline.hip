@@ -28,6 +28,7 @@
 #include <functional>
 #include <vector>
 
+#include "bitmap.hpp"
 #include "bucket.hpp"
 #include "device.hpp"
 #include "runtime.hpp"
@@ -45,6 +46,7 @@ struct Geometry {
     // table's row stride
     int bcoarse[AGNES_MAX_LAYERS], bstride[AGNES_MAX_LAYERS];
     int bstride_max;
+    BitmapPlan bm;                     // bm.use: the hyperbatch samples on per-minibatch bitmaps
 };
 
 // Edge numbers, sort positions and positions in the join of one hop are
@@ -79,6 +81,7 @@ static Geometry plan(const Store& s, int32_t H, int32_t B, const int32_t* fanout
         g.bstride[l] = bucket_table_stride(bb);
         g.bstride_max = std::max(g.bstride_max, g.bstride[l]);
     }
+    g.bm = bitmap_plan(s, H, B, fanouts, L, g.cap);
     return g;
 }
 
@@ -1356,9 +1359,12 @@ __global__ __launch_bounds__(kBlock) void k_stage(const Unit* __restrict__ host,
 // ----------------------------------------------------------------- host orchestration
 
 // Layout of the block that the host reads at the synchronisation point:
-// [Ctl][layer sizes H x (L+1) int32][edge counts H x L int64].
+// [Ctl][layer sizes H x (L+1) int32][edge counts H x L int64][partial
+// statistics][errors H].  On the bitmap path the kernels write the sizes,
+// counts and errors into the pinned block themselves, and the partial
+// statistics (slots) are copied there after the list.
 struct SyncLayout {
-    size_t lsz, ecount, lstat, bytes;
+    size_t lsz, ecount, lstat, copied, err, bytes;   // copied: what the radix path copies to the host
     int n_lstat;                      // workgroups of k_list_stats (one partial pair each)
 };
 
@@ -1370,26 +1376,42 @@ static SyncLayout sync_layout(int H, int L, int64_t rows_max) {
     y.ecount = (y.lsz + (size_t)H * (L + 1) * 4 + 255) / 256 * 256;
     y.lstat = (y.ecount + (size_t)H * L * 8 + 255) / 256 * 256;
     y.n_lstat = list_stats_groups(rows_max);
-    y.bytes = y.lstat + (size_t)y.n_lstat * 16;
+    y.copied = y.lstat + (size_t)y.n_lstat * 16;
+    y.err = y.lstat + std::max((size_t)y.n_lstat * 16, (size_t)kBmListMax * (2 + AGNES_MAX_LAYERS) * 4);
+    y.bytes = y.err + (size_t)H * 4;
     return y;
 }
 
 static void reserve_workspace(Workspace& w, const Geometry& g, const SyncLayout& y) {
     const int64_t H = g.H;
     w.nodes.reserve((size_t)g.rows_max * 4);
-    w.size.reserve((size_t)H * 4);
-    w.newcnt.reserve((size_t)H * 8);
-    w.req_off.reserve((size_t)(H + 1) * 8);
+    w.params.reserve(std::max(sizeof(ChainParams), sizeof(BmParams)));
     w.mb_off.reserve((size_t)(H + 1) * 8);
     w.sync.reserve(y.bytes);
     w.sync_host.reserve(y.bytes);
     w.cnt.reserve((size_t)g.Rmax * 4);
     w.e_off.reserve((size_t)(g.Rmax + 1) * 4);     // edge numbers are below 2^32 (plan)
-    for (int i = 0; i < 2; i++) {
-        w.rl_key[i].reserve((size_t)g.rows_max * 8);
-        w.rl_val[i].reserve((size_t)g.rows_max * 4);
-    }
+    for (int i = 0; i < 2; i++) w.rl_key[i].reserve((size_t)g.rows_max * 8);
     w.skey.reserve((size_t)g.sort_max * 4);
+    w.scan_part.reserve((size_t)scan_partials_needed() * 8);
+    if (!w.ev[0])
+        for (auto& e : w.ev) AGNES_CHECK_HIP(hipEventCreate(&e));
+    if (g.bm.use) {
+        // the list goes to the buffer that does not hold the last hop's node lists
+        w.rl_val[(g.L & 1) ^ 1].reserve((size_t)g.rows_max * 4);
+        w.params_host.reserve(sizeof(BmParams));
+        w.bm_zero.reserve(g.bm.bytes);
+        for (int i = 0; i < 2; i++) w.bm_os[i].reserve((size_t)H * (g.bm.K + 1) * 4);
+        w.bm_rt.reserve((size_t)H * (g.bm.nb + 1) * 4);
+        w.bm_ce.reserve((size_t)H * g.bm.capE * 2);
+        w.bm_tab.reserve((size_t)H * g.bm.capC * (g.bm.K + 1) * 2);
+        w.bm_cbase.reserve((size_t)H * g.bm.capC * 4);
+        return;
+    }
+    w.size.reserve((size_t)H * 4);
+    w.newcnt.reserve((size_t)H * 8);
+    w.req_off.reserve((size_t)(H + 1) * 8);
+    for (int i = 0; i < 2; i++) w.rl_val[i].reserve((size_t)g.rows_max * 4);
     w.sval.reserve((size_t)g.sort_max * 4);
     w.skey2.reserve((size_t)g.sort_max * 4);
     w.sval2.reserve((size_t)g.sort_max * 4);
@@ -1400,11 +1422,7 @@ static void reserve_workspace(Workspace& w, const Geometry& g, const SyncLayout&
     w.acoff.reserve((size_t)(kCoarseMax + 1) * 8);
     w.rs_hist.reserve((size_t)radix_hist_entries(g.sort_max) * 4);
     w.rs_dtot.reserve((size_t)radix_dtot_entries() * 4);
-    w.scan_part.reserve((size_t)scan_partials_needed() * 8);
     w.topo_part.reserve((size_t)((grid_for(g.Rmax, 2048) + kXcds - 1) / kXcds * kXcds) * 4);
-    w.params.reserve(sizeof(ChainParams));
-    if (!w.ev[0])
-        for (auto& e : w.ev) AGNES_CHECK_HIP(hipEventCreate(&e));
 }
 
 template <typename OffT>
@@ -1697,6 +1715,55 @@ static void launch_chain(const Store& s, Batch& b, const Geometry& g, const Sync
     AGNES_CHECK_HIP(hipGetLastError());
 }
 
+// The bitmap path's launches: first the hops (after them the sizes are known
+// to the host), then the list.
+static BitmapArgs bitmap_args(const Store& s, Batch& b, const Geometry& g, const SyncLayout& y,
+                              const int32_t* fanouts, bool captured) {
+    Workspace& w = b.ws;
+    char *dev = w.sync.as<char>(), *host = (char*)w.sync_host.ptr;
+    const int last = g.L & 1;
+    BitmapArgs a{};
+    a.s = &s;
+    a.p = g.bm;
+    a.H = g.H; a.B = g.B; a.L = g.L;
+    a.fanouts = fanouts;
+    a.cap = g.cap;
+    a.capN = g.capN;
+    a.sample_groups = s.sample_groups;
+    a.given = *(const BmParams*)w.params_host.ptr;
+    a.params_host = captured ? (const BmParams*)w.params_host.ptr : nullptr;
+    a.params = w.params.as<BmParams>();
+    a.zero = w.bm_zero.as<char>();
+    a.ctl = (Ctl*)dev;
+    a.lsz = (int32_t*)(dev + y.lsz);
+    a.host_lsz = (int32_t*)(host + y.lsz);
+    a.ecount = (int64_t*)(dev + y.ecount);
+    a.host_ecount = (int64_t*)(host + y.ecount);
+    a.host_err = (uint32_t*)(host + y.err);
+    a.nodes = w.nodes.as<int32_t>();
+    a.deg = w.cnt.as<int32_t>();
+    a.rp = w.e_off.as<uint32_t>();
+    a.cg = w.skey.as<int32_t>();
+    a.ce = w.bm_ce.as<uint16_t>();
+    a.tab = w.bm_tab.as<uint16_t>();
+    a.cbase = w.bm_cbase.as<uint32_t>();
+    for (int i = 0; i < 2; i++) {
+        a.se[i] = w.rl_key[i].as<uint64_t>();
+        a.os[i] = w.bm_os[i].as<int32_t>();
+    }
+    a.rt = w.bm_rt.as<int32_t>();
+    for (int l = 0; l < g.L; l++) {
+        a.row_ptr[l] = b.row_ptr[l].as<int32_t>();
+        a.col[l] = b.col[l].as<int32_t>();
+    }
+    a.list_key = w.rl_key[last ^ 1].as<uint64_t>();
+    a.list_val = w.rl_val[last ^ 1].as<int32_t>();
+    a.node_off = w.mb_off.as<int64_t>();
+    a.nodes_out = b.nodes.as<int32_t>();
+    a.part = (uint32_t*)(dev + y.lstat);
+    return a;
+}
+
 // Everything launch_chain's launches depend on apart from the params block.
 static std::vector<uint64_t> chain_key(const Store& s, const Batch& b, const Geometry& g, const int32_t* fanouts) {
     const Workspace& w = b.ws;
@@ -1709,8 +1776,12 @@ static std::vector<uint64_t> chain_key(const Store& s, const Batch& b, const Geo
     for (const DevBuf* d : {&w.nodes, &w.size, &w.newcnt, &w.req_off, &w.mb_off, &w.sync, &w.cnt, &w.e_off,
                             &w.rl_key[0], &w.rl_key[1], &w.rl_val[0], &w.rl_val[1], &w.skey, &w.sval, &w.skey2,
                             &w.sval2, &w.split, &w.ghist, &w.gemit, &w.rs_hist, &w.rs_dtot, &w.scan_part,
-                            &w.topo_part, &w.params, &w.acoff})
+                            &w.topo_part, &w.params, &w.acoff, &w.bm_zero, &w.bm_os[0], &w.bm_os[1], &w.bm_rt,
+                            &w.bm_ce, &w.bm_tab, &w.bm_cbase})
         k.push_back(a(d->ptr));
+    k.push_back((uint64_t)g.bm.use);
+    k.push_back(a(w.sync_host.ptr));
+    k.push_back(a(w.params_host.ptr));
     for (int l = 0; l < g.L; l++) {
         k.push_back(a(b.row_ptr[l].ptr));
         k.push_back(a(b.col[l].ptr));
@@ -1746,7 +1817,8 @@ static void capture_chain(const Store& s, Batch& b, const Geometry& g, const Syn
     AGNES_CHECK_HIP(hipStreamBeginCapture(b.cap_stream, hipStreamCaptureModeThreadLocal));
     hipGraph_t graph = nullptr;
     try {
-        launch_chain(s, b, g, y, fanouts, s.join_path == 0, b.cap_stream);
+        if (g.bm.use) bitmap_hops(bitmap_args(s, b, g, y, fanouts, true), b.cap_stream);
+        else launch_chain(s, b, g, y, fanouts, s.join_path == 0, b.cap_stream);
     } catch (...) {
         (void)hipStreamEndCapture(b.cap_stream, &graph);
         if (graph) (void)hipGraphDestroy(graph);
@@ -1805,11 +1877,15 @@ void begin_hyperbatch(const Store& s, Batch& b, const int32_t* targets, bool tar
         const size_t tb = (size_t)H * B * sizeof(int32_t);
         w.targets_host.reserve_slack(tb);
         memcpy(w.targets_host.ptr, targets, tb);
-        w.targets.reserve_slack(tb);
-        AGNES_CHECK_HIP(hipMemcpyAsync(w.targets.ptr, w.targets_host.ptr, tb, hipMemcpyHostToDevice, st));
-        targets = w.targets.as<int32_t>();
+        targets = (const int32_t*)w.targets_host.ptr;
+        if (!g.bm.use) {               // (the bitmap path's first kernel reads them from there)
+            w.targets.reserve_slack(tb);
+            AGNES_CHECK_HIP(hipMemcpyAsync(w.targets.ptr, w.targets_host.ptr, tb, hipMemcpyHostToDevice, st));
+            targets = w.targets.as<int32_t>();
+        }
     }
-    AGNES_LAUNCH(k_params, dim3(1), dim3(kBlock), 0, st, w.params.as<ChainParams>(), targets, seed, mb_base,
+    if (g.bm.use) *(BmParams*)w.params_host.ptr = BmParams{targets, seed, mb_base};
+    else AGNES_LAUNCH(k_params, dim3(1), dim3(kBlock), 0, st, w.params.as<ChainParams>(), targets, seed, mb_base,
                        w.sync.as<Ctl>(), (int64_t)H * B);
     AGNES_CHECK_HIP(hipGetLastError());
     // With graph replay, a shape seen twice in a row is captured once and
@@ -1819,17 +1895,39 @@ void begin_hyperbatch(const Store& s, Batch& b, const int32_t* targets, bool tar
     if (replay && !(b.chain && key == b.chain_key) && key == b.last_key)
         capture_chain(s, b, g, y, fanouts, key);
     if (replay && b.chain && key == b.chain_key) AGNES_CHECK_HIP(hipGraphLaunch(b.chain, st));
+    else if (g.bm.use) bitmap_hops(bitmap_args(s, b, g, y, fanouts, false), st);
     else launch_chain(s, b, g, y, fanouts, s.join_path == 0, st);
+    b.bitmap = g.bm.use;
     // what finish needs to sample the hyperbatch again on the radix-sort path
     b.fanouts.assign(fanouts, fanouts + L);
     b.seed = seed;
     b.mb_base = mb_base;
     b.targets_dev = targets;
     b.last_key = std::move(key);
+    if (g.bm.use) {
+        // the sizes of the outputs are in pinned host memory once the hops are
+        // done: finish reads them while the list is built
+        b.ids_in_chain = true;
+        b.cur = (L & 1) ^ 1;
+        b.sampled_at = b.sampled;
+        AGNES_CHECK_HIP(hipEventRecord(b.sampled_at, st));
+        b.state = kSampled;
+        b.listed_at = b.sampled_at;
+        bitmap_list(bitmap_args(s, b, g, y, fanouts, false), st);
+        AGNES_CHECK_HIP(hipMemcpyAsync((char*)w.sync_host.ptr + y.lstat, w.sync.as<char>() + y.lstat,
+                                       (size_t)g.bm.list_groups * (2 + AGNES_MAX_LAYERS) * 4, hipMemcpyDeviceToHost,
+                                       st));
+        b.list_groups = g.bm.list_groups;
+        if (!b.listed) AGNES_CHECK_HIP(hipEventCreateWithFlags(&b.listed, hipEventDisableTiming));
+        b.listed_at = b.prof ? w.ev[1] : b.listed;
+        AGNES_CHECK_HIP(hipEventRecord(b.listed_at, st));
+        return;
+    }
     b.cur = L & 1;                    // the list buffers alternate hop by hop
     // sizes of the outputs travel to pinned host memory; finish reads them
-    AGNES_CHECK_HIP(hipMemcpyAsync(w.sync_host.ptr, w.sync.ptr, y.bytes, hipMemcpyDeviceToHost, st));
+    AGNES_CHECK_HIP(hipMemcpyAsync(w.sync_host.ptr, w.sync.ptr, y.copied, hipMemcpyDeviceToHost, st));
     b.sampled_at = b.prof ? w.ev[1] : b.sampled;
+    b.listed_at = b.sampled_at;
     AGNES_CHECK_HIP(hipEventRecord(b.sampled_at, st));
     b.state = kSampled;
 }
@@ -1843,8 +1941,15 @@ void finish_hyperbatch(Batch& b, hipStream_t st) {
     SyncLayout y = sync_layout(H, L, b.rows_max);
     AGNES_CHECK_HIP(hipEventSynchronize(b.sampled_at));
     b.state = kIdle;   // until the gather is enqueued
-    Ctl hc;
-    memcpy(&hc, w.sync_host.ptr, sizeof(Ctl));
+    Ctl hc{};
+    if (b.bitmap) {
+        const uint32_t* err = (const uint32_t*)((const char*)w.sync_host.ptr + y.err);
+        for (int j = 0; j < H; j++) hc.err |= err[j];
+        // (a batch that is left empty may begin again on another stream)
+        if (hc.err) AGNES_CHECK_HIP(hipEventSynchronize(b.listed_at));
+    } else {
+        memcpy(&hc, w.sync_host.ptr, sizeof(Ctl));
+    }
     if (hc.err & 8) {
         // a sorted sub-bucket exceeded its capacity: the hyperbatch's sampling
         // runs again on the radix-sort path (same results), then as before
@@ -1852,7 +1957,7 @@ void finish_hyperbatch(Batch& b, hipStream_t st) {
         AGNES_LAUNCH(k_params, dim3(1), dim3(kBlock), 0, b.stream, w.params.as<ChainParams>(), b.targets_dev,
                      b.seed, b.mb_base, w.sync.as<Ctl>(), (int64_t)H * b.B);
         launch_chain(s, b, g, y, b.fanouts.data(), true, b.stream);
-        AGNES_CHECK_HIP(hipMemcpyAsync(w.sync_host.ptr, w.sync.ptr, y.bytes, hipMemcpyDeviceToHost, b.stream));
+        AGNES_CHECK_HIP(hipMemcpyAsync(w.sync_host.ptr, w.sync.ptr, y.copied, hipMemcpyDeviceToHost, b.stream));
         AGNES_CHECK_HIP(hipEventRecord(b.sampled_at, b.stream));
         AGNES_CHECK_HIP(hipEventSynchronize(b.sampled_at));
         memcpy(&hc, w.sync_host.ptr, sizeof(Ctl));
@@ -1872,8 +1977,15 @@ void finish_hyperbatch(Batch& b, hipStream_t st) {
         b.stats.sampled[l] = hc.sampled[l];
         b.stats.new_nodes[l] = hc.new_nodes[l];
         b.stats.topo_blocks[l] = hc.topo_blocks[l];
+        if (!b.bitmap) continue;
+        for (int j = 0; j < H; j++) {
+            const int32_t* n = &b.layer_sizes[(size_t)j * (L + 1) + l];
+            b.stats.requests[l] += n[0];
+            b.stats.new_nodes[l] += n[1] - n[0];
+            b.stats.sampled[l] += ecount[(size_t)j * L + l];
+        }
     }
-    {
+    if (!b.bitmap) {
         const uint64_t* lp = (const uint64_t*)((const char*)w.sync_host.ptr + y.lstat);
         int64_t nd = 0, nf = 0;
         for (int i = 0; i < y.n_lstat; i++) {
@@ -1905,7 +2017,7 @@ void finish_hyperbatch(Batch& b, hipStream_t st) {
     b.features.reserve_slack((size_t)std::max<int64_t>(rows, 1) * (size_t)s.row_bytes);
 
     // gather over the final list, ordered after the sampling phase
-    if (st != b.stream) AGNES_CHECK_HIP(hipStreamWaitEvent(st, b.sampled_at, 0));
+    if (st != b.stream) AGNES_CHECK_HIP(hipStreamWaitEvent(st, b.listed_at, 0));
     const uint64_t* rlk = w.rl_key[b.cur].as<uint64_t>();
     const int32_t* rlv = w.rl_val[b.cur].as<int32_t>();
     int32_t* ids = b.ids_in_chain ? nullptr : b.nodes.as<int32_t>();   // else written by the sampling phase
@@ -2027,6 +2139,17 @@ void wait_batch(Batch& b) {
     AGNES_REQUIRE(b.state == kGathering, AGNES_ERR_INVALID, "the batch holds no finished hyperbatch");
     AGNES_CHECK_HIP(hipEventSynchronize(b.gathered_at));
     b.stats.sample_ms = b.stats.gather_ms = b.stats.copy_ms = -1.0f;
+    if (b.bitmap) {
+        // the partial statistics, copied before the gather
+        const SyncLayout y = sync_layout(b.H, b.L, b.rows_max);
+        const uint32_t* p = (const uint32_t*)((const char*)b.ws.sync_host.ptr + y.lstat);
+        int64_t sum[2 + AGNES_MAX_LAYERS] = {};
+        for (int g = 0; g < b.list_groups; g++)
+            for (int i = 0; i < 2 + b.L; i++) sum[i] += p[g * (2 + AGNES_MAX_LAYERS) + i];
+        b.stats.distinct_rows = sum[0];
+        b.stats.feat_blocks = sum[1];
+        for (int l = 0; l < b.L; l++) b.stats.topo_blocks[l] = sum[2 + l];
+    }
     if (b.prof) {
         Workspace& w = b.ws;
         AGNES_CHECK_HIP(hipEventElapsedTime(&b.stats.sample_ms, w.ev[0], w.ev[1]));

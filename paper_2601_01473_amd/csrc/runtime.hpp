@@ -192,6 +192,11 @@ struct Workspace {
     DevBuf topo_part;                 // per sampler workgroup: Bck rows it opened
     DevBuf acoff;                     // node-range buckets: old list entries before each coarse bucket
     DevBuf params;                    // per-call values the sampling kernels read (targets, seed, minibatch base)
+    PinnedBuf params_host;            // bitmap path: the same, read by its first kernel
+    DevBuf bm_zero;                   // bitmap path: counters and bits cleared at the start of a hyperbatch
+    DevBuf bm_ce, bm_tab, bm_cbase;   // bitmap path: places of the sampled neighbours, runs and chunks
+    DevBuf bm_os[2];                  // bitmap path: list entries before every node range, per minibatch
+    DevBuf bm_rt;                     // bitmap path: list entries before every list block, per minibatch
     DevBuf targets;                   // targets uploaded from host memory by the call
     PinnedBuf targets_host;           // their pinned staging copy
     DevBuf blk_flag, blk_off;         // staged tier: flags over the final list and their offsets
@@ -227,6 +232,14 @@ struct Store {
     int nlev = 0;
     std::vector<int32_t> lev_info_host;
     DevBuf bnd, lev_info;
+    // Bitmap path (bitmap.hip): list blocks, and tables of node ranges (their
+    // bounds, then the list block that each begins with), of about equal
+    // in-degree weight.
+    struct RangeTable { int at, count, longest; };
+    RangeTable range_tab[6] = {};
+    int64_t n_list_blocks = 0;
+    int n_list_spans = 0;
+    DevBuf list_blocks, list_spans, ranges;
     int join_path = 0;                // 1 = node-range buckets, 0 = radix sort and merge-path join (default)
     int bucket_cap = 2048;            // entries of a sorted sub-bucket (at most kBucketCap)
     int sample_groups = 0;            // most workgroups of a sampling-phase kernel that loops over its
@@ -286,6 +299,11 @@ struct Batch {
     // the same points (one marker fewer per phase on the stream).
     int prof = 0;
     hipEvent_t sampled_at = nullptr, gathered_at = nullptr;
+    // The end of the sampling phase's last kernel: on the bitmap path the list
+    // is built after the sizes are known, otherwise the same as sampled_at.
+    hipEvent_t listed = nullptr, listed_at = nullptr;
+    int list_groups = 0;              // bitmap path: rows of partial statistics
+    bool bitmap = false;              // the hyperbatch samples on per-minibatch bitmaps
     hipEvent_t needed = nullptr;      // staged tier: the needed feature blocks are in ws.need_host
     int64_t capN = 0;
     int64_t rows_max = 0;             // node-list capacity of the hyperbatch (sizes the sync block)
@@ -333,6 +351,7 @@ struct Batch {
         if (chain) (void)hipGraphExecDestroy(chain);
         if (cap_stream) (void)hipStreamDestroy(cap_stream);
         if (sampled) (void)hipEventDestroy(sampled);
+        if (listed) (void)hipEventDestroy(listed);
         if (gathered) (void)hipEventDestroy(gathered);
         if (needed) (void)hipEventDestroy(needed);
         if (sage_ev) (void)hipEventDestroy(sage_ev);
