@@ -26,6 +26,7 @@
 #include <algorithm>
 #include <cstring>
 #include <functional>
+#include <type_traits>
 #include <vector>
 
 #include "bitmap.hpp"
@@ -932,6 +933,22 @@ __global__ __launch_bounds__(kBlock) void k_list_stats(const uint64_t* rl_key, u
 // ----------------------------------------------------------------- gather
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+// Sixteen bytes at a 4-byte boundary: pieces of rows of at least 16 bytes that
+// are no multiple of 16.  A row's last piece ends with the row and overlaps the
+// one before it.
+typedef u32x4 u32x4p __attribute__((aligned(4)));
+struct Piece {
+    u32x4p v;
+};
+
+// Element c of row `row` of rows of row_units units (Piece: of row_units words).
+template <typename Unit>
+__device__ __forceinline__ int64_t unit_at(int64_t row, int64_t row_units, int64_t c) {
+    return row * row_units + c;
+}
+__device__ __forceinline__ int64_t piece_at(int64_t row, int64_t words, int64_t c) {
+    return row * words + (c * 4 < words - 4 ? c * 4 : words - 4);
+}
 
 // Source row of node u in the staged tier: its feature-cache row when it has
 // one (the cache rows follow the pool's), else row (u mod rpb) of the pool
@@ -960,6 +977,8 @@ __device__ __forceinline__ uint32_t source_row(const int32_t* tbuf, uint32_t rpb
 // A launch covers list entries [base, base + rows); the host may split the list
 // into several launches so that other streams' kernels are dispatched between
 // them.
+// Unit = Piece: row_units counts 4-byte words (300-byte rows: 295 thousand rows
+// copied word by word, 64 lanes and then 11 per row, took 52 us).
 template <typename Unit, int LPR, int U, bool NT, bool ONE, bool TIER>
 __global__ __launch_bounds__(kBlock) void k_gather(const Unit* __restrict__ feat, Unit* __restrict__ out,
                                                    int32_t* __restrict__ nodes_out,
@@ -968,6 +987,7 @@ __global__ __launch_bounds__(kBlock) void k_gather(const Unit* __restrict__ feat
                                                    int H, int64_t base, int64_t rows, int64_t row_units,
                                                    const int32_t* __restrict__ tbuf, uint32_t rpb,
                                                    const int32_t* __restrict__ tch, uint32_t pool_rows) {
+    constexpr bool PIECES = std::is_same<Unit, Piece>::value;
     constexpr int RPW = kWave / LPR;             // lane groups (rows) per wave
     constexpr int GPB = kWavesPerBlock * RPW;    // lane groups per workgroup
     extern __shared__ int64_t node_off[];
@@ -976,6 +996,7 @@ __global__ __launch_bounds__(kBlock) void k_gather(const Unit* __restrict__ feat
     const int li = lane_id() % LPR;
     const int gid = wave_id() * RPW + lane_id() / LPR;
     const int64_t lo = base, hi = base + rows;
+    const int64_t units = PIECES ? (row_units + 3) / 4 : row_units;
     const int64_t stride = (int64_t)G * GPB * U;
     for (int64_t e0 = lo + ((int64_t)blockIdx.x * GPB + gid) * U; e0 < hi; e0 += stride) {
         uint64_t key[U];
@@ -1000,21 +1021,30 @@ __global__ __launch_bounds__(kBlock) void k_gather(const Unit* __restrict__ feat
             dst[k] = d;
             if (nodes_out && ok[k] && li == 0) nodes_out[d] = (int32_t)u;
         }
-        const int64_t c_end = ONE ? std::min<int64_t>(row_units, li + 1) : row_units;
+        const int64_t c_end = ONE ? std::min<int64_t>(units, li + 1) : units;
         for (int64_t c = li; c < c_end; c += LPR) {
-            Unit x[U];
+            typename std::conditional<PIECES, u32x4, Unit>::type x[U];
 #pragma unroll
             for (int k = 0; k < U; k++)
-                if (fresh[k]) x[k] = feat[(int64_t)src[k] * row_units + c];
+                if (fresh[k]) {
+                    if constexpr (PIECES) x[k] = *(const u32x4p*)((const uint32_t*)feat + piece_at(src[k], row_units, c));
+                    else x[k] = feat[unit_at<Unit>(src[k], row_units, c)];
+                }
 #pragma unroll
             for (int k = 1; k < U; k++)
                 if (!fresh[k]) x[k] = x[k - 1];
 #pragma unroll
             for (int k = 0; k < U; k++) {
                 if (!ok[k]) continue;
-                Unit* o = out + (int64_t)dst[k] * row_units + c;
-                if (NT) __builtin_nontemporal_store(x[k], o);
-                else *o = x[k];
+                if constexpr (PIECES) {
+                    u32x4p* o = (u32x4p*)((uint32_t*)out + piece_at(dst[k], row_units, c));
+                    if (NT) __builtin_nontemporal_store(x[k], o);
+                    else *o = x[k];
+                } else {
+                    Unit* o = out + unit_at<Unit>(dst[k], row_units, c);
+                    if (NT) __builtin_nontemporal_store(x[k], o);
+                    else *o = x[k];
+                }
             }
         }
     }
@@ -1137,7 +1167,7 @@ static void launch_gather_k(const GatherArgs& a, int groups, hipStream_t st) {
     // dispatch order through the list
     constexpr int64_t per_wg = (int64_t)kWavesPerBlock * (kWave / LPR) * U;
     const int G = (int)std::max<int64_t>(1, std::min<int64_t>(groups, (a.rows + per_wg - 1) / per_wg));
-    const bool one = a.row_units <= LPR;
+    const bool one = (std::is_same<Unit, Piece>::value ? (a.row_units + 3) / 4 : a.row_units) <= LPR;
     if (a.tbuf) {
         if (one) launch_gather_k2<Unit, LPR, U, NT, true, true>(a, G, st);
         else launch_gather_k2<Unit, LPR, U, NT, false, true>(a, G, st);
@@ -1199,24 +1229,39 @@ static void launch_gather(const GatherArgs& all, int groups, int unroll, bool nt
     // entries also let more repeats of a node reuse its row; 4 elsewhere, where
     // more rows in flight cost occupancy (2 KiB rows hold two pieces per lane)
     // or lane groups already keep enough bytes moving.
-    if (unroll == 0) unroll = (sizeof(Unit) == 16 && all.row_units >= 64 && all.row_units < 128) ? 16 : 4;
+    const int64_t units = std::is_same<Unit, Piece>::value ? (all.row_units + 3) / 4 : all.row_units;
+    if (unroll == 0) unroll = (std::is_same<Unit, u32x4>::value && units >= 64 && units < 128) ? 16 : 4;
     chunks = (int)std::max<int64_t>(1, std::min<int64_t>(chunks, all.rows));
     for (int c = 0; c < chunks; c++) {
         GatherArgs a = all;
         a.base = all.base + all.rows * c / chunks;
         a.rows = all.base + all.rows * (c + 1) / chunks - a.base;
         const int G = std::max(8, groups / chunks);
-        if (a.row_units >= 64 && sizeof(Unit) == 16) {
-            if (a.row_units >= 128) launch_gather_rows_upr<2>(a, G, unroll, nt, st);
-            else launch_gather_rows_upr<1>(a, G, unroll, nt, st);
-        } else if (a.row_units >= 64) launch_gather_lpr<Unit, 64>(a, G, unroll, nt, st);
-        else if (a.row_units > 16) launch_gather_lpr<Unit, 32>(a, G, unroll, nt, st);
-        else if (a.row_units > 8) launch_gather_lpr<Unit, 16>(a, G, unroll, nt, st);
-        else if (a.row_units > 4) launch_gather_lpr<Unit, 8>(a, G, unroll, nt, st);
+        if constexpr (std::is_same<Unit, u32x4>::value) {
+            if (units >= 64) {
+                if (units >= 128) launch_gather_rows_upr<2>(a, G, unroll, nt, st);
+                else launch_gather_rows_upr<1>(a, G, unroll, nt, st);
+                continue;
+            }
+        }
+        if (units > 32) launch_gather_lpr<Unit, 64>(a, G, unroll, nt, st);
+        else if (units > 16) launch_gather_lpr<Unit, 32>(a, G, unroll, nt, st);
+        else if (units > 8) launch_gather_lpr<Unit, 16>(a, G, unroll, nt, st);
+        else if (units > 4) launch_gather_lpr<Unit, 8>(a, G, unroll, nt, st);
         else launch_gather_lpr<Unit, 4>(a, G, unroll, nt, st);
     }
 }
 
+// The row copy of a store's hyperbatch: whole 16-byte units, 16-byte pieces at
+// 4-byte boundaries, or (rows under 16 bytes) 4-byte words.
+static void copy_rows(const Store& s, GatherArgs a, hipStream_t st) {
+    const bool wide = s.row_bytes % 16 == 0;
+    a.row_units = wide ? s.row_bytes / 16 : s.row_bytes / 4;
+    const bool nt = s.gather_nt != 0;
+    if (wide) launch_gather<u32x4>(a, s.gather_groups, s.gather_unroll, nt, s.gather_chunks, st);
+    else if (s.row_bytes > 16) launch_gather<Piece>(a, s.gather_groups, s.gather_unroll, nt, s.gather_chunks, st);
+    else launch_gather<uint32_t>(a, s.gather_groups, s.gather_unroll, nt, s.gather_chunks, st);
+}
 
 // ----------------------------------------------------------------- staged feature tier
 //
@@ -2023,12 +2068,6 @@ void finish_hyperbatch(Batch& b, hipStream_t st) {
     int32_t* ids = b.ids_in_chain ? nullptr : b.nodes.as<int32_t>();   // else written by the sampling phase
     GatherArgs ga{s.features.ptr, b.features.ptr, ids, rlk, rlv, w.mb_off.as<int64_t>(),
                   H, 0, rows, 0, nullptr, (uint32_t)s.rpb};
-    const bool wide = s.row_bytes % 16 == 0;
-    ga.row_units = wide ? s.row_bytes / 16 : s.row_bytes / 4;
-    auto copy_rows = [&](const GatherArgs& a) {
-        if (wide) launch_gather<u32x4>(a, s.gather_groups, s.gather_unroll, s.gather_nt != 0, s.gather_chunks, st);
-        else launch_gather<uint32_t>(a, s.gather_groups, s.gather_unroll, s.gather_nt != 0, s.gather_chunks, st);
-    };
     memset(&b.tier, 0, sizeof(b.tier));
     if (s.tiered && rows > 0) {
         // The needed blocks are found and read back on this hyperbatch's
@@ -2097,7 +2136,7 @@ void finish_hyperbatch(Batch& b, hipStream_t st) {
             GatherArgs a = ga;
             a.base = r.e0;
             a.rows = r.e1 - r.e0;
-            if (a.rows > 0) copy_rows(a);
+            if (a.rows > 0) copy_rows(s, a, st);
         }
         if (cache) {
             // access counts, then admissions in ascending node order while the cache has room
@@ -2123,7 +2162,7 @@ void finish_hyperbatch(Batch& b, hipStream_t st) {
         AGNES_CHECK_HIP(hipEventRecord(s.pool_free, st));
     } else {
         if (b.prof) AGNES_CHECK_HIP(hipEventRecord(w.ev[2], st));
-        if (rows > 0) copy_rows(ga);
+        if (rows > 0) copy_rows(s, ga, st);
         AGNES_CHECK_HIP(hipGetLastError());
     }
     // the end of the gather (after the tier counters' copy): what wait waits for
