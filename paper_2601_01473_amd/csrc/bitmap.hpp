@@ -81,7 +81,7 @@ struct BitmapArgs {
     int32_t* list_val;
     int64_t* node_off;        // [H+1]
     int32_t* nodes_out;
-    uint32_t* part;           // [list_groups][2 + AGNES_MAX_LAYERS] distinct rows, feature blocks, topology blocks
+    uint32_t* part;           // pinned: [list_groups][2 + AGNES_MAX_LAYERS] distinct rows, feature blocks, topology blocks
 };
 
 BitmapPlan bitmap_plan(const Store& s, int H, int B, const int32_t* fanouts, int L, const int64_t* cap);

@@ -1406,8 +1406,7 @@ __global__ __launch_bounds__(kBlock) void k_stage(const Unit* __restrict__ host,
 // Layout of the block that the host reads at the synchronisation point:
 // [Ctl][layer sizes H x (L+1) int32][edge counts H x L int64][partial
 // statistics][errors H].  On the bitmap path the kernels write the sizes,
-// counts and errors into the pinned block themselves, and the partial
-// statistics (slots) are copied there after the list.
+// counts, errors and partial statistics into the pinned block themselves.
 struct SyncLayout {
     size_t lsz, ecount, lstat, copied, err, bytes;   // copied: what the radix path copies to the host
     int n_lstat;                      // workgroups of k_list_stats (one partial pair each)
@@ -1805,7 +1804,7 @@ static BitmapArgs bitmap_args(const Store& s, Batch& b, const Geometry& g, const
     a.list_val = w.rl_val[last ^ 1].as<int32_t>();
     a.node_off = w.mb_off.as<int64_t>();
     a.nodes_out = b.nodes.as<int32_t>();
-    a.part = (uint32_t*)(dev + y.lstat);
+    a.part = (uint32_t*)(host + y.lstat);
     return a;
 }
 
@@ -1959,9 +1958,6 @@ void begin_hyperbatch(const Store& s, Batch& b, const int32_t* targets, bool tar
         b.state = kSampled;
         b.listed_at = b.sampled_at;
         bitmap_list(bitmap_args(s, b, g, y, fanouts, false), st);
-        AGNES_CHECK_HIP(hipMemcpyAsync((char*)w.sync_host.ptr + y.lstat, w.sync.as<char>() + y.lstat,
-                                       (size_t)g.bm.list_groups * (2 + AGNES_MAX_LAYERS) * 4, hipMemcpyDeviceToHost,
-                                       st));
         b.list_groups = g.bm.list_groups;
         if (!b.listed) AGNES_CHECK_HIP(hipEventCreateWithFlags(&b.listed, hipEventDisableTiming));
         b.listed_at = b.prof ? w.ev[1] : b.listed;
