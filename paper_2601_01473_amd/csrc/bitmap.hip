@@ -40,12 +40,6 @@ namespace agnes {
 
 // ----------------------------------------------------------------- plan
 
-static int log2_ceil(int64_t n) {
-    int b = 0;
-    while (((int64_t)1 << b) < n) b++;
-    return b;
-}
-
 constexpr int kTicketStride = 32;                  // tickets lie on lines of their own: atomics on one line serialize
 constexpr int kRunBlocks = 4;                      // list blocks of a run at most
 
@@ -228,22 +222,20 @@ __device__ __forceinline__ void wave_lds_fence() {
 
 // ----------------------------------------------------------------- targets
 
-// Workgroup j < H: minibatch j's targets become its first B nodes; their sorted
-// list, degrees and the row starts of hop 0.  A target out of range or given
-// twice leaves the minibatch empty and is reported.  Every workgroup clears a
-// share of the block that the later kernels count in.
-template <typename OffT, int M>
+// Workgroup j < H: minibatch j's targets become its first B nodes, with their
+// degrees and the row starts of hop 0.  A target out of range or given twice
+// (found by a hash table in LDS) leaves the minibatch empty and is reported.
+// Every workgroup clears a share of the block that the later kernels count in.
+template <typename OffT>
 __global__ __launch_bounds__(kBmThreads) void k_bm_init(BmParams given, const BmParams* prm_host, BmParams* prm, int H, int B, int L,
-                                                        int64_t num_nodes, int64_t capN, int64_t capR,
-                                                        const int32_t* bounds, int K, int P, int32_t f,
-                                                        const OffT* off, int32_t* nodes, int32_t* deg,
-                                                        uint32_t* rp, uint64_t* se, int32_t* os, int32_t* lsz,
-                                                        int32_t* host_lsz, int64_t* ecount, int64_t* host_ecount,
-                                                        uint32_t* host_err, uint4* zero, int64_t zero_pieces,
-                                                        Ctl* ctl) {
-    constexpr int T = kBmThreads;
-    extern __shared__ __align__(16) uint64_t init_sm[];
-    uint64_t* srt = init_sm;                       // (target, index), P of them (a power of two), to be sorted
+                                                        int64_t num_nodes, int64_t capN, int64_t capR, int32_t f,
+                                                        int slots, const OffT* off, int32_t* nodes, int32_t* deg, uint32_t* rp,
+                                                        int32_t* lsz, int32_t* host_lsz, int64_t* ecount,
+                                                        int64_t* host_ecount, uint32_t* host_err, uint4* zero,
+                                                        int64_t zero_pieces, Ctl* ctl) {
+    constexpr int T = kBmThreads, M = kBmMaxB / T;
+    static_assert(kBmMaxB % T == 0);
+    extern __shared__ __align__(16) uint32_t seen[];   // [slots], a power of two, at least 2 B
     __shared__ uint32_t lds[T / kWave];
     __shared__ uint32_t bad;
     const int t = threadIdx.x, j = blockIdx.x;
@@ -251,6 +243,7 @@ __global__ __launch_bounds__(kBmThreads) void k_bm_init(BmParams given, const Bm
         zero[i] = uint4{0u, 0u, 0u, 0u};
     if (j >= H) return;
     if (t == 0) bad = 0;
+    for (int i = t; i < slots; i += T) seen[i] = ~0u;
     if (j == 0) {
         int64_t* c = (int64_t*)ctl;
         for (int i = t; i < (int)(sizeof(Ctl) / 8); i += T) c[i] = 0;
@@ -258,109 +251,77 @@ __global__ __launch_bounds__(kBmThreads) void k_bm_init(BmParams given, const Bm
     }
     const int32_t* targets = (prm_host ? prm_host->targets : given.targets) + (int64_t)j * B;
     __syncthreads();
-    // bitonic sort of P = 2^n >= B keys, key i = m T + t in a register of thread
-    // t: strides below a wave by shuffles, up to T / 2 through LDS, above
-    // between a thread's own registers
-    uint64_t key[M];
+    int32_t d[M];
 #pragma unroll
     for (int m = 0; m < M; m++) {
         const int i = m * T + t;
-        key[m] = ~0ull;
-        if (i < B) {
-            int32_t v = targets[i];
-            if (v < 0 || v >= num_nodes) {
-                atomicOr(&bad, 1u);
-                v = 0;
-            }
-            nodes[(int64_t)j * capN + i] = v;
-            key[m] = ((uint64_t)(uint32_t)v << 32) | (uint32_t)i;
+        d[m] = 0;
+        if (i >= B) continue;
+        int32_t v = targets[i];
+        if (v < 0 || v >= num_nodes) {
+            atomicOr(&bad, 1u);
+            v = 0;
         }
+        nodes[(int64_t)j * capN + i] = v;
+        d[m] = (int32_t)(off[v + 1] - off[v]);
+        // (at least half of the slots stay free, so the search ends)
+        uint32_t at = ((uint32_t)v * 2654435761u) >> 16 & (slots - 1), was;
+        while ((was = atomicCAS(&seen[at], ~0u, (uint32_t)v)) != ~0u && was != (uint32_t)v) at = (at + 1) & (slots - 1);
+        if (was != ~0u) atomicOr(&bad, 2u);
     }
-    for (int size = 2; size <= P; size <<= 1) {
-        for (int d = size >> 1; d > 0; d >>= 1) {
-            if (d >= T) {
-#pragma unroll
-                for (int m = 0; m < M; m++) {
-                    const int o = m ^ (d / T);
-                    if (o <= m || o >= M) continue;
-                    const bool up = ((m * T) & size) == 0;
-                    const uint64_t a = key[m], b = key[o];
-                    if ((a > b) == up) {
-                        key[m] = b;
-                        key[o] = a;
-                    }
-                }
-                continue;
-            }
-            uint64_t other[M];
-            if (d >= kWave) {
-                __syncthreads();
-#pragma unroll
-                for (int m = 0; m < M; m++)
-                    if (m * T + t < P) srt[m * T + t] = key[m];
-                __syncthreads();
-#pragma unroll
-                for (int m = 0; m < M; m++) other[m] = m * T + t < P ? srt[(m * T + t) ^ d] : ~0ull;
-            } else {
-#pragma unroll
-                for (int m = 0; m < M; m++) other[m] = shfl64(key[m], lane_id() ^ d);
-            }
-#pragma unroll
-            for (int m = 0; m < M; m++) {
-                const int i = m * T + t;
-                const bool low = ((i & d) == 0) == ((i & size) == 0);   // this key keeps the smaller one
-                if ((other[m] < key[m]) == low) key[m] = other[m];
-            }
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < M; m++)
-        if (m * T + t < P) srt[m * T + t] = key[m];
-    __syncthreads();
-    for (int i = t; i < B; i += T) {
-        const uint64_t key = srt[i];
-        if (i > 0 && (srt[i - 1] >> 32) == (key >> 32)) atomicOr(&bad, 2u);
-        se[(int64_t)j * capN + i] = key;
-    }
-    __syncthreads();
-    const bool ok = bad == 0;
     uint32_t run = 0;
-    for (int i0 = 0; i0 < B; i0 += T) {
-        const int i = i0 + t;
-        int32_t d = 0;
-        uint32_t k = 0;
-        if (i < B) {
-            const int32_t v = nodes[(int64_t)j * capN + i];
-            d = (int32_t)(off[v + 1] - off[v]);
-            k = (uint32_t)(d < f ? d : f);
-        }
+#pragma unroll
+    for (int m = 0; m < M; m++) {
+        if (m * T >= B) break;
+        const int i = m * T + t;
         uint32_t tot;
-        const uint32_t ex = wg_exclusive_scan<T>(k, lds, tot);
+        const uint32_t ex = wg_exclusive_scan<T>((uint32_t)(d[m] < f ? d[m] : f), lds, tot);
         if (i < B) {
-            deg[(int64_t)j * capR + i] = d;
+            deg[(int64_t)j * capR + i] = d[m];
             rp[(int64_t)j * capR + i] = run + ex;
         }
         run += tot;
     }
-    for (int k = t; k <= K; k += T) {
-        int lo = 0;
-        if (ok) {
-            const uint32_t v = (uint32_t)bounds[k];
-            int hi = B;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if ((uint32_t)(srt[mid] >> 32) < v) lo = mid + 1; else hi = mid;
-            }
-        }
-        os[(int64_t)j * (K + 1) + k] = lo;
-    }
     if (t == 0) {
+        const bool ok = bad == 0;                      // (the scan's barriers lie between)
         const int64_t e = ok ? (int64_t)run : 0;
         lsz[(int64_t)j * (L + 1)] = host_lsz[(int64_t)j * (L + 1)] = ok ? B : 0;
         ecount[(int64_t)j * L] = host_ecount[(int64_t)j * L] = e;
         host_err[j] = bad;
     }
+}
+
+// Minibatch j's sorted (target, index) list and how many of its targets lie below
+// every range, by counting: part x of j's workgroups takes the x-th 256 of the
+// B + K + 1 questions "how many targets lie below this", each against all targets
+// in LDS (four per read).  The first union needs the answers, the sampling of hop
+// 0 does not, so these workgroups run beside that hop's sampling.  As a bitonic
+// sort in the kernel before it: 16.6 + 17.5 us for the two kernels at 32 x 1024
+// targets of 2^20 nodes, fanout 15, now 7.7 + 18.6; 22.6 + 27.9 at 64 x 1024 of
+// 2^23, fanout 25, now 12.8 + 31.5.  (The same sort by one workgroup of the
+// sampling launch outlasts the sampling: 27 us.)
+// (Targets given twice would share a place, but then the minibatch is empty.)
+// sm: ceil(B / 4) uint4.
+__device__ __forceinline__ void place_targets(uint4* sm, int j, int part, int B, int L, int K, const int32_t* bounds,
+                                              const int32_t* lsz, const int32_t* nodes, int64_t capN, uint64_t* se,
+                                              int32_t* os) {
+    uint32_t* tg = (uint32_t*)sm;
+    const int pieces = (B + 3) / 4;
+    const bool ok = lsz[(int64_t)j * (L + 1)] > 0;
+    nodes += (int64_t)j * capN;
+    for (int i = threadIdx.x; i < 4 * pieces; i += kBlock) tg[i] = i < B ? (uint32_t)nodes[i] : ~0u;
+    const int q = part * kBlock + (int)threadIdx.x, k = q - B;
+    const uint32_t own = q >= B && k <= K ? (uint32_t)bounds[k] : 0u;
+    __syncthreads();
+    const uint32_t v = q < B ? tg[q] : own;
+    uint32_t below = 0;
+#pragma unroll 4
+    for (int i = 0; i < pieces; i++) {
+        const uint4 x = sm[i];
+        below += (uint32_t)(x.x < v) + (uint32_t)(x.y < v) + (uint32_t)(x.z < v) + (uint32_t)(x.w < v);
+    }
+    if (q < B) se[(int64_t)j * capN + below] = ((uint64_t)v << 32) | (uint32_t)q;
+    else if (k <= K) os[(int64_t)j * (K + 1) + k] = ok ? (int32_t)below : 0;
 }
 
 // ----------------------------------------------------------------- sampling
@@ -384,6 +345,7 @@ __global__ __launch_bounds__(kBmThreads) void k_bm_init(BmParams given, const Bm
 // touches (plain stores of a byte each: counting them here, with an atomic per
 // request, ran at the rate of a few cache lines, 100 instead of 27 us for 138
 // thousand requests).
+// The first `sorts` workgroups of hop 0 place the targets.
 // Dynamic LDS: first row pointers [H+1], row offsets [CR], neighbours [CR f],
 // sizes [H], range bounds [K+1], run ends [K], row nodes, degrees and first
 // edges [CR each], places [CR f] and rows, then ranges [CR f] (16-bit).
@@ -394,8 +356,15 @@ __global__ __launch_bounds__(kBlock) void k_bm_sample(int l, int L, int H, int32
                                                       int64_t capE, int64_t capC, int K, const int32_t* bounds,
                                                       const int32_t* lsz, const int64_t* ecount, const uint32_t* rp,
                                                       int32_t* cg, uint16_t* ce, uint16_t* tab, uint32_t* cbase,
-                                                      int32_t* row_ptr, uint8_t* tmark) {
+                                                      int32_t* row_ptr, uint8_t* tmark, int sorts, int B,
+                                                      uint64_t* se, int32_t* os) {
     extern __shared__ __align__(16) int64_t rpo[];
+    if ((int)blockIdx.x < sorts) {
+        const int parts = (B + K + kBlock) / kBlock, j = (int)blockIdx.x / parts;
+        if (j < H) place_targets((uint4*)rpo, j, (int)blockIdx.x % parts, B, L, K, bounds, lsz, nodes, capN, se, os);
+        return;
+    }
+    const int bid = (int)blockIdx.x - sorts, bids = (int)gridDim.x - sorts;   // (sorts: a multiple of kXcds)
     OffT* soff = (OffT*)(rpo + H + 1);
     int32_t* su = (int32_t*)(soff + CR);
     int32_t* size = su + CR * f;
@@ -432,9 +401,9 @@ __global__ __launch_bounds__(kBlock) void k_bm_sample(int l, int L, int H, int32
     const int64_t mb_base = prm->mb_base;
     const int64_t items = (int64_t)((smax + CR - 1) / CR) * H;
     const int64_t per = (items + kXcds - 1) / kXcds;
-    const int64_t lo = std::min<int64_t>(items, (int64_t)(blockIdx.x % kXcds) * per);
+    const int64_t lo = std::min<int64_t>(items, (int64_t)(bid % kXcds) * per);
     const int64_t hi = std::min<int64_t>(items, lo + per);
-    const int64_t step = gridDim.x / kXcds;
+    const int64_t step = bids / kXcds;
     // the next request's node and row start are loaded while this one is sampled
     auto request = [&](int64_t x, int& j, int& r, int32_t& v, uint32_t& e) {
         const int c = (int)(x / H);
@@ -446,7 +415,7 @@ __global__ __launch_bounds__(kBlock) void k_bm_sample(int l, int L, int H, int32
             e = rp[(int64_t)j * capR + r];
         }
     };
-    int64_t x = lo + blockIdx.x / kXcds;
+    int64_t x = lo + bid / kXcds;
     int jn = 0, rn = -1;
     int32_t vn = 0;
     uint32_t en = 0;
@@ -1261,30 +1230,28 @@ static void hops(const BitmapArgs& a, hipStream_t st) {
     const BitmapPlan& p = a.p;
     const OffT* off = s.offsets.as<OffT>();
     const int H = a.H, L = a.L;
-    const int P = 1 << log2_ceil(std::max(a.B, 2));
     const int extra = (int)std::min<int64_t>(64, (int64_t)(p.bytes >> 16));
-#define AGNES_BM_INIT(M)                                                                                          \
-    AGNES_LAUNCH((k_bm_init<OffT, M>), dim3(H + extra), dim3(kBmThreads), (size_t)P * 8, st, a.given,             \
-                 a.params_host, a.params, H, a.B, L, s.num_nodes, a.capN, p.capR, p.bounds, p.K, P, a.fanouts[0], off, a.nodes,  \
-                 a.deg, a.rp, a.se[0], a.os[0], a.lsz, a.host_lsz, a.ecount, a.host_ecount, a.host_err,           \
-                 (uint4*)a.zero, (int64_t)(p.bytes / 16), a.ctl)
-    if (P <= kBmThreads) AGNES_BM_INIT(1);
-    else if (P <= 2 * kBmThreads) AGNES_BM_INIT(2);
-    else AGNES_BM_INIT(4);
-#undef AGNES_BM_INIT
+    int slots = 64;                                    // (8192 at most, 32 KiB)
+    while (slots < 2 * a.B) slots <<= 1;
+    AGNES_LAUNCH((k_bm_init<OffT>), dim3(H + extra), dim3(kBmThreads), (size_t)slots * 4, st, a.given, a.params_host, a.params, H, a.B, L,
+                 s.num_nodes, a.capN, p.capR, a.fanouts[0], slots, off, a.nodes, a.deg, a.rp, a.lsz, a.host_lsz, a.ecount,
+                 a.host_ecount, a.host_err, (uint4*)a.zero, (int64_t)(p.bytes / 16), a.ctl);
     const size_t union_lds = (size_t)p.range_max / 256 * 36;
     for (int l = 0; l < L; l++) {
         const int32_t f = a.fanouts[l];
         const int cur = l & 1, CR = chunk_rows(f);
         const int most = a.sample_groups > 0 ? a.sample_groups : 2048;
         const int g = xcd_grid((int64_t)H * ((a.cap[l] + CR - 1) / CR), most);
-        const size_t sample_lds = (size_t)(H + 1) * 8 + (size_t)CR * (sizeof(OffT) + 12) + (size_t)CR * f * 8 +
-                                  (size_t)(H + 2 * p.K + 1) * 4;
+        const int sorts = l == 0 ? (H * ((a.B + p.K + kBlock) / kBlock) + kXcds - 1) / kXcds * kXcds : 0;
+        const size_t sample_lds = std::max((size_t)(H + 1) * 8 + (size_t)CR * (sizeof(OffT) + 12) + (size_t)CR * f * 8 +
+                                               (size_t)(H + 2 * p.K + 1) * 4,
+                                           sorts > 0 ? (size_t)(a.B + 3) / 4 * 16 : (size_t)0);
         uint8_t* tm = (uint8_t*)(a.zero + p.tmark) + (int64_t)l * p.tmarks;
 #define AGNES_BM_SAMPLE(MK)                                                                                    \
-    AGNES_LAUNCH((k_bm_sample<OffT, MK>), dim3(g), dim3(kBlock), sample_lds, st, l, L, H, f, CR, a.params,      \
+    AGNES_LAUNCH((k_bm_sample<OffT, MK>), dim3(sorts + g), dim3(kBlock), sample_lds, st, l, L, H, f, CR, a.params,      \
                  off, s.indices.as<int32_t>(), s.e_blk_log2, s.nblk, a.nodes, a.capN, p.capR, p.capE, p.capC,  \
-                 p.K, p.bounds, a.lsz, a.ecount, a.rp, a.cg, a.ce, a.tab, a.cbase, a.row_ptr[l], tm)
+                 p.K, p.bounds, a.lsz, a.ecount, a.rp, a.cg, a.ce, a.tab, a.cbase, a.row_ptr[l], tm, sorts, a.B,    \
+                 a.se[0], a.os[0])
         // (the pairs compared grow with the square of the bound: common fanouts get their own)
         if (f <= 5) AGNES_BM_SAMPLE(5);
         else if (f <= 10) AGNES_BM_SAMPLE(10);

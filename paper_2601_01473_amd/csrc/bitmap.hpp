@@ -12,11 +12,11 @@ namespace agnes {
 struct Store;
 struct Ctl;
 
-constexpr int kBmThreads = 1024;              // workgroup of the first kernel (the targets' sort)
+constexpr int kBmThreads = 1024;              // workgroup of the first kernel
 constexpr int kBmStage = 4096;                // neighbours that a sampling chunk holds in LDS
 constexpr int kBmListNodes = 512;             // nodes of one list block at most
 constexpr int kBmMaxH = 128;                  // minibatches
-constexpr int kBmMaxB = 4096;                 // targets per minibatch (sorted by one workgroup)
+constexpr int kBmMaxB = 4096;                 // targets per minibatch (all in LDS, to be placed)
 constexpr int kBmMaxK = 256;                  // node ranges
 constexpr int kBmListMax = 4096;              // workgroups of the list kernel, each a row of partial statistics
 constexpr int kRangeTables = 6;               // tables of about 1, 2, 4, .. 32 ranges of equal weight
