@@ -91,7 +91,7 @@ def algorithmic_bytes(st: dict, offset_bytes: int, row_bytes: int, ids_in_copy: 
         bs += R * (4 + 2 * offset_bytes + 4) + 8 * S + 4 * U
     bg = st["rows"] * (4 + row_bytes) + st["distinct_rows"] * row_bytes
     # the row-copy kernel moves the rows; the sampling phase packs the output
-    # node ids (k_list_stats), except on the node-range bucket path, where the
+    # node ids (k_bm_list, k_list_stats), except on the node-range bucket path, where the
     # row copy writes them
     copy = bg if ids_in_copy else bg - st["rows"] * 4
     return bs, bg, copy
@@ -576,7 +576,7 @@ def main():
     ap.add_argument("--sampling-groups", type=int, default=None,
                     help="most workgroups of each sampling-phase kernel that loops over its work")
     ap.add_argument("--join-path", type=int, choices=[0, 1], default=None,
-                    help="0: radix sort and merge-path join (default); 1: node-range buckets")
+                    help="0: bitmaps, or radix sort and merge-path join (default); 1: node-range buckets")
     ap.add_argument("--sampling-graph", type=int, choices=[0, 1, 2], default=2,
                     help="1: replay the sampling kernels from a captured HIP graph; 0: launch them one by one; "
                          "2: replay for shapes of at most 2^20 sampled edges (the library's default)")

@@ -295,7 +295,8 @@ agnes_status agnes_set_device_allocator(agnes_device_alloc_fn alloc, agnes_devic
  *     shortens small, launch-bound hyperbatches but slows large hyperbatches
  *     that sample concurrently on several streams.
  *   AGNES_OPT_JOIN_PATH: how each hop unites the sampled neighbours with the
- *     nodes already held and relabels them.  0 (default): a device-wide radix
+ *     nodes already held and relabels them.  0 (default): per-minibatch bitmaps
+ *     where they are the faster path for the shape, else a device-wide radix
  *     sort of the sampled neighbours and a merge-path join with the list;
  *     1: node-range buckets, each joined in workgroup memory (a dense
  *     (node, minibatch) table for narrow buckets such as one hub, a sort in
@@ -305,11 +306,11 @@ agnes_status agnes_set_device_allocator(agnes_device_alloc_fn alloc, agnes_devic
  *     is sampled again with the radix sort (same results); a smaller value
  *     only makes that happen more often.
  *   AGNES_OPT_SAMPLING_GROUPS: most workgroups of each sampling-phase kernel
- *     that loops over its work (the sampler, the radix passes, the join), in
+ *     that loops over its work (the sampler, the radix passes, the join, the list), in
  *     [256, 4096]; 0 (default) chooses per hop: the power of two at or below
  *     its bound of sampled edges (H x frontier capacity x fanout) / 32768,
- *     within [512, 2048].  4096
- *     leaves each kernel at its own limit, 2048 for most.  Fewer need fewer
+ *     within [512, 2048] (on the bitmap path 2048 for the sampler and 1024 for
+ *     the list).  4096 leaves each kernel at its own limit, 2048 for most.  Fewer need fewer
  *     dispatch slots beside a running row copy of another hyperbatch, which
  *     holds most of them; a large hop needs more to hide its latency.
  * Options change launch shapes and store kinds only, never results. */

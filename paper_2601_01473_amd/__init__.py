@@ -153,7 +153,8 @@ class Store:
 
     def set_join_path(self, buckets: bool = True, bucket_cap: int | None = None) -> None:
         """buckets=True: node-range buckets joined in workgroup memory;
-        False: the device-wide radix sort and merge-path join (the store's
+        False: per-minibatch bitmaps or, where it is faster, the
+        device-wide radix sort and merge-path join (the store's
         default).  bucket_cap: entries of one sorted bucket before the
         hyperbatch is sampled again with the radix sort (never changes
         results)."""

@@ -6,7 +6,9 @@
 // (node, minibatch) pairs of the hyperbatch, sorted by node id and then by
 // minibatch.  Objects are stored in ascending node order, so a block's row of
 // Bck is a contiguous run of this list, and a node needed by several
-// minibatches is a run inside it.  Each hop (Alg. 1, sampling loop):
+// minibatches is a run inside it.  Most hyperbatches are sampled on
+// per-minibatch bitmaps, which build that list after the last hop (bitmap.hip;
+// bitmap_plan holds the rule).  The others hop by hop (Alg. 1, sampling loop):
 //   counts      k = min(deg, f_l) per request, in (minibatch, row) order, with
 //               the reduce pass of the edge-offset scan (k_count_reduce)
 //   scan        edge offset of every request (the hop's row pointers)
@@ -1933,7 +1935,8 @@ void begin_hyperbatch(const Store& s, Batch& b, const int32_t* targets, bool tar
                        w.sync.as<Ctl>(), (int64_t)H * B);
     AGNES_CHECK_HIP(hipGetLastError());
     // With graph replay, a shape seen twice in a row is captured once and
-    // then replayed: one graph launch instead of about 20 launches per hop.
+    // then replayed: one graph launch instead of 2 launches per hop (about 20
+    // on the radix-sort path).
     std::vector<uint64_t> key = chain_key(s, b, g, fanouts);
     const bool replay = replay_chain(s, g, fanouts);
     if (replay && !(b.chain && key == b.chain_key) && key == b.last_key)

@@ -161,3 +161,19 @@ def test_bad_targets_leave_the_batch_usable(agnes):
         ref = oracle.Oracle(off, idx).hyperbatch(good, [5, 5], 1, 0)
         for j in range(4):
             compare_minibatch(got[j], ref[j], oracle.gather(feature_bytes(feat), ref[j].nodes), tag=(bad, j))
+
+
+@pytest.mark.parametrize("B,a,b", [(2, 0, 1), (257, 0, 256), (1024, 511, 1023), (1025, 0, 1024), (4096, 1024, 4095)])
+def test_duplicate_targets_are_found_at_any_distance(agnes, B, a, b):
+    n = 20000
+    off, idx = skewed_graph(n, 4, 23)
+    store = agnes.Store(off, idx, features(n, 4, 2), 4096)
+    t = draw_targets(n, 2, B, 29)
+    t[1, b] = t[1, a]
+    with pytest.raises(agnes.AgnesError, match="twice"):
+        store.prepare(t, [3], seed=1)
+    t = np.ascontiguousarray(np.arange(2 * B, dtype=np.int32).reshape(2, B) * 2)      # consecutive hash slots
+    got = store.prepare(t, [3], seed=1).to_host()
+    ref = oracle.Oracle(off, idx).hyperbatch(t, [3], 1, 0)
+    for j in range(2):
+        assert np.array_equal(got[j]["nodes"], ref[j].nodes)

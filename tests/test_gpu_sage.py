@@ -82,6 +82,14 @@ def test_fp16_features(agnes, dims):
     run(agnes, off, idx, feat, None, feat.astype(np.float64), tg, [5, 5], dims, seed=2)
 
 
+@pytest.mark.parametrize("dim", [32, 96])
+def test_fp16_own_rows_and_means_in_one_step_of_the_product(agnes, dim):
+    off, idx = random_graph(1500, 9, 5)
+    tg = distinct_targets(1500, 3, 50, 3)
+    feat = features(1500, dim, 3, np.float16)
+    run(agnes, off, idx, feat, None, feat.astype(np.float64), tg, [5, 3], [dim, dim, 32], seed=3)
+
+
 def test_bf16_features(agnes):
     off, idx = random_graph(1500, 8, 7)
     tg = distinct_targets(1500, 2, 33, 9)
