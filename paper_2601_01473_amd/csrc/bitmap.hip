@@ -115,9 +115,9 @@ BitmapPlan bitmap_plan(const Store& s, int H, int B, const int32_t* fanouts, int
     // allows (0.01 with 16 KiB of bits, 0.02 with 32, 0.06 with 64); the radix
     // path about 75 more per hop for its launches, and 0.06 per thousand edges.
     // Measured per prepare, bitmaps / radix, 32-byte rows, average degree 6 at
-    // 2^25 nodes and 4 at 2^26: taken by the rule 148 / 201 (2^25 nodes, 1 x 64,
-    // [5, 5]), 181 / 247 (2^25, 8 x 256, [10, 5]), 206 / 259 (2^23, 64 x 64,
-    // [5, 5]), 937 / 1013 (2^23, 128 x 1024, [25, 10]), 193 / 197 (2^26, 1 x 64);
+    // 2^25 nodes and 4 at 2^26: taken by the rule 126 / 206 (2^25 nodes, 1 x 64,
+    // [5, 5]), 158 / 258 (2^25, 8 x 256, [10, 5]), 187 / 266 (2^23, 64 x 64,
+    // [5, 5]), 920 / 1031 (2^23, 128 x 1024, [25, 10]), 173 / 204 (2^26, 1 x 64);
     // left to the radix path 1333 / 1103 (2^25, 64 x 1024, [15, 10, 5]),
     // 412 / 289 (2^26, 16 x 1024, [10, 5]), 4627 / 1581 (2^26, 128 x 1024,
     // [15, 10, 5]).  More than kBmMaxH minibatches take LDS for their masks in the
