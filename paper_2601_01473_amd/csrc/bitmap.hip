@@ -672,8 +672,8 @@ __global__ __launch_bounds__(T, 6) void k_bm_union(
     __shared__ uint16_t run_len[kUnRuns];
     __shared__ uint32_t lds[W];
     __shared__ int64_t lds64[W];
-    __shared__ int64_t sh_before;
-    __shared__ int sh_k;
+    __shared__ int64_t sh_before, sh_edges;              // (two words: no barrier need lie between the first's readers
+    __shared__ int sh_k;                                 // and the second's writer where a range has no new nodes)
     const int t = threadIdx.x, w = t / kWave, lane = lane_id();
     const int parts = f_next >= 0 ? K + 1 : K;            // with the held nodes' row starts
     const int j = (int)((blockIdx.x / kXcds) / parts) * kXcds + (int)(blockIdx.x % kXcds);
@@ -939,10 +939,10 @@ __global__ __launch_bounds__(T, 6) void k_bm_union(
     if (f_next >= 0) {
         if (w == 0) {
             const int64_t v = status_sum(st2 + (int64_t)j * (K + 1), k + 1);
-            if (lane == 0) sh_before = v;
+            if (lane == 0) sh_edges = v;
         }
         __syncthreads();
-        const uint32_t base = (uint32_t)sh_before;        // (this workgroup's row starts are written: barriers between)
+        const uint32_t base = (uint32_t)sh_edges;        // (this workgroup's row starts are written: barriers between)
         for (uint32_t i = t; i < nn; i += T) rp[(int64_t)j * capR + first + i] += base;
         if (k == K - 1 && t == 0) {
             const int64_t e = (int64_t)base + run;
