@@ -1899,6 +1899,7 @@ void begin_hyperbatch(const Store& s, Batch& b, const int32_t* targets, bool tar
     reserve_workspace(w, g, y);
     b.rows_max = g.rows_max;
     if (!b.sampled) AGNES_CHECK_HIP(hipEventCreateWithFlags(&b.sampled, hipEventDisableTiming));
+    if (!b.listed) AGNES_CHECK_HIP(hipEventCreateWithFlags(&b.listed, hipEventDisableTiming));
     if (!b.gathered) AGNES_CHECK_HIP(hipEventCreateWithFlags(&b.gathered, hipEventDisableTiming));
     if (!b.sage_done) AGNES_CHECK_HIP(hipEventCreateWithFlags(&b.sage_done, hipEventDisableTiming));
     b.d_lsz = (const int32_t*)((const char*)w.sync.ptr + y.lsz);
@@ -1962,7 +1963,6 @@ void begin_hyperbatch(const Store& s, Batch& b, const int32_t* targets, bool tar
         b.listed_at = b.sampled_at;
         bitmap_list(bitmap_args(s, b, g, y, fanouts, false), st);
         b.list_groups = g.bm.list_groups;
-        if (!b.listed) AGNES_CHECK_HIP(hipEventCreateWithFlags(&b.listed, hipEventDisableTiming));
         b.listed_at = b.prof ? w.ev[1] : b.listed;
         AGNES_CHECK_HIP(hipEventRecord(b.listed_at, st));
         return;
@@ -1985,12 +1985,18 @@ void finish_hyperbatch(Batch& b, hipStream_t st) {
     SyncLayout y = sync_layout(H, L, b.rows_max);
     AGNES_CHECK_HIP(hipEventSynchronize(b.sampled_at));
     b.state = kIdle;   // until the gather is enqueued
+    // A batch that an exception leaves idle may begin again on another stream
+    // and give its buffers to other kernels: the list must be done with them.
+    struct IdleAfterList {
+        const Batch& b;
+        ~IdleAfterList() {
+            if (b.state == kIdle) (void)hipEventSynchronize(b.listed_at);
+        }
+    } idle_after_list{b};
     Ctl hc{};
     if (b.bitmap) {
         const uint32_t* err = (const uint32_t*)((const char*)w.sync_host.ptr + y.err);
         for (int j = 0; j < H; j++) hc.err |= err[j];
-        // (a batch that is left empty may begin again on another stream)
-        if (hc.err) AGNES_CHECK_HIP(hipEventSynchronize(b.listed_at));
     } else {
         memcpy(&hc, w.sync_host.ptr, sizeof(Ctl));
     }

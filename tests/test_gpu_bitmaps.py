@@ -13,6 +13,7 @@ import torch
 import oracle
 from tests.graphs import features
 from tests.parity import compare_minibatch, feature_bytes, log
+from tests.test_gpu_robustness import _failing_allocator
 
 pytestmark = pytest.mark.gpu
 
@@ -161,6 +162,35 @@ def test_bad_targets_leave_the_batch_usable(agnes):
         ref = oracle.Oracle(off, idx).hyperbatch(good, [5, 5], 1, 0)
         for j in range(4):
             compare_minibatch(got[j], ref[j], oracle.gather(feature_bytes(feat), ref[j].nodes), tag=(bad, j))
+
+
+def test_failing_finish_leaves_nothing_running(agnes):
+    """The rows find no memory while the list is still being built on the sampling
+    stream: when finish has raised, that stream is idle, and the batch may begin
+    again on another one."""
+    off, idx = skewed_graph(1 << 20, 6, 14)
+    store = agnes.Store(off, idx, features(1 << 20, 1, 1), 4096)
+    large, small = draw_targets(1 << 20, 128, 1024, 14), draw_targets(1 << 20, 3, 50, 15)
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    state = {"calls": 0, "fail_at": -1}
+    agnes.agnes_set_device_allocator(*_failing_allocator(agnes, state))
+    try:
+        for step in range(3):
+            log("failing finish", step)
+            b = store.begin(large, [10, 8], seed=step, stream=s1)
+            state["fail_at"] = state["calls"]
+            with pytest.raises(agnes.AgnesError, match="no memory"):
+                b.finish(stream=s2)
+            assert s1.query()
+            b = store.begin(small, [5, 5], seed=1, batch=b, stream=s2).finish(stream=s1)
+            got = b.to_host()
+            ref = oracle.Oracle(off, idx).hyperbatch(small, [5, 5], 1, 0)
+            for j in range(3):
+                compare_minibatch(got[j], ref[j], tag=(step, j))
+            b.close()
+        store.close()
+    finally:
+        agnes.agnes_set_device_allocator(None, None)
 
 
 @pytest.mark.parametrize("B,a,b", [(2, 0, 1), (257, 0, 256), (1024, 511, 1023), (1025, 0, 1024), (4096, 1024, 4095)])
