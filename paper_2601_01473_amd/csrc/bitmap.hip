@@ -128,6 +128,13 @@ BitmapPlan bitmap_plan(const Store& s, int H, int B, const int32_t* fanouts, int
     return p;
 }
 
+void bitmap_key(const BitmapPlan& p, std::vector<uint64_t>& key) {
+    const auto a = [](const void* x) { return (uint64_t)(uintptr_t)x; };
+    const uint64_t v[] = {(uint64_t)p.use, (uint64_t)p.K, (uint64_t)p.range_max, (uint64_t)p.nb, a(p.bounds),
+                          a(p.blocks), (uint64_t)p.capR, (uint64_t)p.capE, (uint64_t)p.capC, (uint64_t)p.tmarks};
+    key.insert(key.end(), v, v + sizeof(v) / sizeof(v[0]));
+}
+
 // ----------------------------------------------------------------- device helpers
 
 __device__ __forceinline__ uint64_t status_load(const uint64_t* p) {

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "../../include/agnes.h"
 
 namespace agnes {
@@ -85,6 +87,9 @@ struct BitmapArgs {
 };
 
 BitmapPlan bitmap_plan(const Store& s, int H, int B, const int32_t* fanouts, int L, const int64_t* cap);
+// What captured launches of the plan depend on, appended to `key`: two stores of
+// one size, one after the other at the same addresses, differ in their node ranges.
+void bitmap_key(const BitmapPlan& p, std::vector<uint64_t>& key);
 // The sampling kernels up to the last hop's union: when they are done the
 // layer sizes, edge counts and errors are in the pinned block.
 void bitmap_hops(const BitmapArgs& a, hipStream_t st);

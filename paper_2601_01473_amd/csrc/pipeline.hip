@@ -1825,7 +1825,7 @@ static std::vector<uint64_t> chain_key(const Store& s, const Batch& b, const Geo
                             &w.topo_part, &w.params, &w.acoff, &w.bm_zero, &w.bm_os[0], &w.bm_os[1], &w.bm_rt,
                             &w.bm_ce, &w.bm_tab, &w.bm_cbase})
         k.push_back(a(d->ptr));
-    k.push_back((uint64_t)g.bm.use);
+    bitmap_key(g.bm, k);
     k.push_back(a(w.sync_host.ptr));
     k.push_back(a(w.params_host.ptr));
     for (int l = 0; l < g.L; l++) {

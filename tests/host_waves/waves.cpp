@@ -5,6 +5,7 @@
 // highest first, which shows accesses that no barrier orders.  Workgroups run one
 // after the other, so a wait for a later one ends the program.
 //
+// waves keys: exit status 0 if plans that launch differently have different keys.
 // waves IN OUT: reads sizes, graph, targets, node ranges and list blocks, runs one
 // hyperbatch and writes its sizes, lists, CSR blocks and statistics.
 #include <stdio.h>
@@ -142,8 +143,33 @@ static void write_array(FILE* f, const T* p, size_t n) {
     fwrite(p, sizeof(T), n, f);
 }
 
-int main(int, char** argv) {
+// Two stores of one size, the second where the first one was, cut differently.
+static bool keys_differ() {
     using namespace agnes;
+    const int32_t fanouts[] = {10, 5};
+    const int64_t cap[] = {256, 2816, 16384};
+    auto key = [&](int ranges, int longest, int64_t blocks, char* bounds) {
+        static Store s;
+        s.num_nodes = 16384;
+        s.num_edges = 16384 * 8;
+        s.nblk = 128;
+        for (auto& t : s.range_tab) t = Store::RangeTable{0, ranges, longest};
+        s.n_list_blocks = blocks;
+        s.ranges.ptr = bounds;
+        std::vector<uint64_t> k;
+        bitmap_key(bitmap_plan(s, 8, 256, fanouts, 2, cap), k);
+        s.ranges.ptr = nullptr;
+        return k;
+    };
+    char at[8];
+    const auto k = key(8, 4096, 1024, at);
+    return k == key(8, 4096, 1024, at) && k != key(9, 4096, 1024, at) && k != key(8, 4352, 1024, at) &&
+           k != key(8, 4096, 1025, at) && k != key(8, 4096, 1024, at + 4);
+}
+
+int main(int argc, char** argv) {
+    using namespace agnes;
+    if (argc == 2) return keys_differ() ? 0 : 1;
     FILE* in = fopen(argv[1], "rb");
     if (!in) die("no input");
     const int64_t* h = read_array<int64_t>(in, 12);

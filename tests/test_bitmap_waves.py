@@ -62,7 +62,12 @@ def waves(tmp_path_factory):
         assert at[0] == len(data)
         return out
 
+    run.exe, run.env = str(exe), env
     return run
+
+
+def test_stores_cut_differently_have_different_launch_keys(waves):
+    assert subprocess.run([waves.exe, "keys"], env=waves.env).returncode == 0
 
 
 def check(waves, off, idx, targets, fan, bounds, seed=3, mb=2, rpb=16, e_blk_log2=5):

@@ -164,6 +164,38 @@ def test_bad_targets_leave_the_batch_usable(agnes):
             compare_minibatch(got[j], ref[j], oracle.gather(feature_bytes(feat), ref[j].nodes), tag=(bad, j))
 
 
+def test_replay_on_a_store_that_takes_the_place_of_another(agnes):
+    """A batch whose sampling was captured, on a second store of the same size at the
+    first one's address but with other degrees, and so other node ranges."""
+    n, fan = 5000, [6, 4]
+    off, idx = skewed_graph(n, 6, 16, heavy=0.9)
+    even = np.sort(np.random.default_rng(17).integers(0, n, len(idx)).astype(np.int32).reshape(-1))
+    feat, t = features(n, 4, 1), draw_targets(n, 8, 100, 16)
+    for attempt in range(8):
+        first = agnes.Store(off, idx, feat, 4096)
+        first.set_sampling_graph(True)
+        b = None
+        for step in range(3):
+            b = first.prepare(t, fan, seed=step, batch=b)
+        at = first.handle
+        first.close()
+        second = agnes.Store(off, even, feat, 4096)
+        second.set_sampling_graph(True)
+        log("second store", attempt, second.handle == at)
+        if second.handle != at:
+            b.close()
+            second.close()
+            continue
+        for step in range(3):
+            b = second.prepare(t, fan, seed=step, batch=b)
+            got = b.to_host()
+            ref = oracle.Oracle(off, even).hyperbatch(t, fan, step, 0)
+            for j in range(8):
+                compare_minibatch(got[j], ref[j], oracle.gather(feature_bytes(feat), ref[j].nodes), tag=(step, j))
+        return
+    pytest.skip("no second store at the first one's address")
+
+
 def test_failing_finish_leaves_nothing_running(agnes):
     """The rows find no memory while the list is still being built on the sampling
     stream: when finish has raised, that stream is idle, and the batch may begin
