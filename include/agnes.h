@@ -23,6 +23,9 @@
  *   - AGNES_WIDE_OFFSETS=1: agnes_build_blocks* keep int64 CSR offsets 64-bit
  *     on the device; by default the offsets of a graph with fewer than 2^31
  *     edges are stored as int32.  Read at every build.
+ *   - AGNES_RADIX_JOIN=1: the store's hyperbatches are never sampled on
+ *     per-minibatch bitmaps (AGNES_OPT_JOIN_PATH 0 is the radix sort and
+ *     merge-path join for every shape).  Read at every build.
  */
 #ifndef AGNES_H
 #define AGNES_H

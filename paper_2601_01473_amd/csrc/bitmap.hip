@@ -123,7 +123,7 @@ BitmapPlan bitmap_plan(const Store& s, int H, int B, const int32_t* fanouts, int
     // [15, 10, 5]).  More than kBmMaxH minibatches take LDS for their masks in the
     // list kernel: 2034 / 1798 at 2^23, 256 x 1024, [25, 10].
     const double wg = p.range_max <= (1 << 17) ? 0.01 : p.range_max <= (1 << 18) ? 0.02 : 0.06;
-    p.use = s.join_path == 0 && H <= kBmMaxH && B <= kBmMaxB && p.K <= kBmMaxK && p.capE < ((int64_t)1 << 31) &&
+    p.use = s.join_path == 0 && s.bitmaps && H <= kBmMaxH && B <= kBmMaxB && p.K <= kBmMaxK && p.capE < ((int64_t)1 << 31) &&
             (int64_t)L * s.nblk <= ((int64_t)1 << 26) && (double)H * p.K * L * wg <= 75.0 * L + 6e-5 * H * edges;
     return p;
 }

@@ -240,7 +240,8 @@ struct Store {
     int64_t n_list_blocks = 0;
     int n_list_spans = 0;
     DevBuf list_blocks, list_spans, ranges;
-    int join_path = 0;                // 1 = node-range buckets, 0 = radix sort and merge-path join (default)
+    int join_path = 0;                // 1 = node-range buckets, 0 = bitmaps, or radix sort and merge-path join (default)
+    int bitmaps = 1;                  // 0 = join path 0 is the radix sort and merge-path join for every shape
     int bucket_cap = 2048;            // entries of a sorted sub-bucket (at most kBucketCap)
     int sample_groups = 0;            // most workgroups of a sampling-phase kernel that loops over its
                                       // work; 0 = chosen per hop by its size

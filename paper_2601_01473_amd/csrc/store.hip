@@ -104,6 +104,10 @@ Store* build_store(const agnes_csr* csr, const agnes_features* feat, uint64_t bl
     const char* wide = std::getenv("AGNES_WIDE_OFFSETS");
     const bool narrow = o64 && e < 0x7FFFFFFFll && !(wide && wide[0] == '1');
     s->offsets64 = (o64 && !narrow) ? 1 : 0;
+    // AGNES_RADIX_JOIN=1 keeps this store's hyperbatches off the bitmap path (so
+    // that the radix sort and the merge-path join can be tested on small shapes).
+    const char* radix = std::getenv("AGNES_RADIX_JOIN");
+    s->bitmaps = radix && radix[0] == '1' ? 0 : 1;
     s->block_bytes = (int64_t)block_bytes;
     s->e_blk = (int64_t)block_bytes / 4;
     s->e_blk_log2 = 0;

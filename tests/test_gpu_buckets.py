@@ -1,5 +1,6 @@
 """The node-range bucket join (AGNES_OPT_JOIN_PATH = 1) on the GPU, through the
-C ABI, element by element against the oracle and against the radix-sort join:
+C ABI, element by element against the oracle, beside the radix-sort join and the
+default path (per-minibatch bitmaps, for these shapes):
 
 - random graphs with hubs, several minibatch counts and fanouts, int32 and
   int64 offsets;
@@ -32,25 +33,24 @@ def agnes():
 
 
 def _both_paths(ag, off, idx, feat, tg, fan, seed, mb_base, block_bytes, tag, cap=None):
-    store = ag.Store(off, idx, feat, block_bytes)
     got = {}
-    for path in (1, 0):
-        store.set_join_path(bool(path), bucket_cap=cap if path else None)
+    for path in ("buckets", "radix", "default"):
+        with pytest.MonkeyPatch.context() as env:
+            env.setenv("AGNES_RADIX_JOIN", "1" if path == "radix" else "0")
+            store = ag.Store(off, idx, feat, block_bytes)
+        store.set_join_path(path == "buckets", bucket_cap=cap if path == "buckets" else None)
         b = store.prepare(tg, fan, seed=seed, mb_base=mb_base)
         got[path] = (b.to_host(), b.stats())
         b.close()
+        store.close()
     ref = oracle.Oracle(off, idx).hyperbatch(tg, fan, seed, mb_base)
     fb = feature_bytes(feat)
-    for j in range(tg.shape[0]):
-        compare_minibatch(got[1][0][j], ref[j], oracle.gather(fb, ref[j].nodes), tag=(tag, "buckets", j))
     want = oracle.hyperbatch_stats(off, block_bytes, fb.shape[1], ref, len(fan))
-    for k, v in want.items():
-        assert got[1][1][k] == v, (tag, k, got[1][1][k], v)
-        assert got[0][1][k] == v, (tag, "radix", k, got[0][1][k], v)
-    for j in range(tg.shape[0]):
-        for k in ("nodes", "features"):
-            assert np.array_equal(got[0][0][j][k], got[1][0][j][k]), (tag, j, k)
-    store.close()
+    for path, (mbs, stats) in got.items():
+        for j in range(tg.shape[0]):
+            compare_minibatch(mbs[j], ref[j], oracle.gather(fb, ref[j].nodes), tag=(tag, path, j))
+        for k, v in want.items():
+            assert stats[k] == v, (tag, path, k, stats[k], v)
 
 
 @pytest.mark.parametrize("n,H,B,fan,o32", [

@@ -108,8 +108,11 @@ def test_config_c5_hyperbatch_sweep(agnes, H):
     run_config(agnes, "c5", H=H)
 
 
-def test_config_c2_with_64_minibatches(agnes):
+@pytest.mark.parametrize("radix", [False, True])
+def test_config_c2_with_64_minibatches(agnes, radix, monkeypatch):
     """C2's graph (20-bit node ids: two radix passes of 10-bit digits) with 64
     minibatches: the last hop's bound (64 x 16384 x 10 edges) is above 8M keys,
-    where 8-bit digits would take 8192-key tiles; 10-bit digits keep 4096."""
+    where 8-bit digits would take 8192-key tiles; on the radix path 10-bit
+    digits keep 4096.  The default path takes bitmaps."""
+    monkeypatch.setenv("AGNES_RADIX_JOIN", "1" if radix else "0")
     run_config(agnes, "c2", H=64)

@@ -2,8 +2,8 @@
 oracle: graph size, degree skew (hubs, isolated nodes, repeated edges), H, B,
 hop count and fanouts (0, below and above typical degrees), int32 and int64
 offsets (int64 also kept 64-bit on the device), row widths and dtypes, block
-sizes, the sampling kernels' workgroup cap and graph replay.  Every case runs
-twice on one batch with new targets, seed and minibatch base (the second call
+sizes, the sampling kernels' workgroup cap and graph replay, each on the default
+path (bitmaps, for these shapes) and on the radix sort.  Every case runs twice on one batch with new targets, seed and minibatch base (the second call
 replays the sampling kernels from a graph when the shape is small enough)."""
 import os
 
@@ -51,9 +51,15 @@ def _case(seed):
                 dtype=dtype, dim=dim, bb=bb, groups=groups, graph=graph)
 
 
+def _path(monkeypatch, radix):
+    monkeypatch.setenv("AGNES_RADIX_JOIN", "1" if radix else "0")
+
+
+@pytest.mark.parametrize("radix", [False, True])
 @pytest.mark.parametrize("seed", range(N_CASES))
-def test_random_shape_matches_oracle(agnes, seed, monkeypatch):
+def test_random_shape_matches_oracle(agnes, seed, radix, monkeypatch):
     c = _case(seed)
+    _path(monkeypatch, radix)
     log("fuzz", seed, {k: (v.__name__ if isinstance(v, type) else v) for k, v in c.items()})
     off, idx = random_graph(c["n"], c["avg"], 2000 + seed, hubs=c["hubs"], hub_deg=c["hub_deg"], multi=c["multi"])
     if c["o32"]:
@@ -101,13 +107,15 @@ def _large_case(seed):
     return dict(scale=scale, ef=ef, abc=abc, n=n, H=H, B=B, fan=fan, groups=groups)
 
 
+@pytest.mark.parametrize("radix", [False, True])
 @pytest.mark.parametrize("seed", range(N_LARGE))
-def test_random_rmat_shape_matches_oracle(agnes, seed):
+def test_random_rmat_shape_matches_oracle(agnes, seed, radix, monkeypatch):
     """Larger R-MAT graphs (2^12 to 2^17 nodes, three skews) with hyperbatches
     of up to 256 x 1024 targets: join groups take several tiles each and the
     sampling kernels loop; every minibatch is compared with the oracle."""
     import synth
     c = _large_case(seed)
+    _path(monkeypatch, radix)
     log("fuzz large", seed, c)
     off, idx = synth.rmat_csr(c["scale"], c["ef"], c["abc"], 6000 + seed)
     feat = features(c["n"], 16, 7000 + seed)
@@ -129,14 +137,17 @@ def test_random_rmat_shape_matches_oracle(agnes, seed):
     store.close()
 
 
+@pytest.mark.parametrize("radix", [False, True])
 @pytest.mark.parametrize("scale,abc", [(21, (0.57, 0.19, 0.19)), (22, (0.45, 0.25, 0.15))])
-def test_rmat_large_sort_tiles_match_oracle(agnes, scale, abc):
+def test_rmat_large_sort_tiles_match_oracle(agnes, scale, abc, radix, monkeypatch):
     """2^21 and 2^22 nodes (three radix passes of 8-bit digits) with 64 x 1024
     targets and fanouts [25, 10]: the last hop's bound (about 17 M edges) is
-    above 8 M keys, so its sort takes the 8192-key tiles; every minibatch is
+    above 8 M keys, so the radix path's sort takes the 8192-key tiles; on the
+    default path, hundreds of new nodes per range.  Every minibatch is
     compared with the oracle, and every gathered row through the oracle's
     gather on four of them."""
     import synth
+    _path(monkeypatch, radix)
     off, idx = synth.rmat_csr(scale, 16, abc, 9000 + scale)
     n = 1 << scale
     feat = features(n, 16, 9100 + scale)
