@@ -31,6 +31,7 @@
 // workgroups that already run, and these publish before they wait.  A status
 // word carries its value and its flag, so no fence is needed.
 #include <algorithm>
+#include <cmath>
 
 #include "bitmap.hpp"
 #include "device.hpp"
@@ -55,6 +56,79 @@ static int chunk_rows(int f) {
     int r = f <= 32 ? kBlock : 16;
     while (r > 1 && (int64_t)r * f > kBmStage) r >>= 1;
     return r;
+}
+
+// Class of a count: 0, 1, 2 to 3, 4 to 7, ...
+static int log2_class(uint64_t x) { return x ? 64 - __builtin_clzll(x) : 0; }
+
+void build_degree_classes(Store& s, const std::vector<uint32_t>& indeg, const agnes_csr& csr) {
+    constexpr int C = 33;
+    std::vector<double> count(C * C, 0.0), sum(C * C, 0.0), in(C, 0.0);
+    for (int64_t v = 0; v < csr.num_nodes; v++) {
+        const int64_t d = csr.offsets_dtype == AGNES_INT64
+                              ? ((const int64_t*)csr.offsets)[v + 1] - ((const int64_t*)csr.offsets)[v]
+                              : ((const int32_t*)csr.offsets)[v + 1] - ((const int32_t*)csr.offsets)[v];
+        const int c = log2_class(indeg[(size_t)v]), x = c * C + log2_class((uint64_t)d);
+        count[x] += 1.0;
+        sum[x] += (double)d;
+        in[c] += (double)indeg[(size_t)v];
+    }
+    s.degrees.clear();
+    for (int c = 0; c < C; c++) {
+        Store::DegreeClass k{0.0, in[c] / std::max(1.0, (double)csr.num_edges), {}};
+        for (int x = c * C; x < (c + 1) * C; x++) {
+            if (count[x] == 0.0) continue;
+            k.cells.push_back(Store::DegreeCell{count[x], sum[x] / count[x]});
+            k.nodes += count[x];
+        }
+        if (k.nodes > 0.0) s.degrees.push_back(k);
+    }
+}
+
+// Targets are any nodes alike, a sampled neighbour is a node in proportion to
+// its in-degree, and nodes that several edges reach count once.  (Within 10 % of
+// what is sampled on R-MAT graphs of degree 16, 20 and 60 and on a regular one,
+// 1024 and 4096 targets, 2 and 3 hops.)
+double expected_edges(const Store& s, int B, const int32_t* fanouts, int L) {
+    std::vector<double> held(s.degrees.size());
+    for (size_t c = 0; c < held.size(); c++) held[c] = B * s.degrees[c].nodes / (double)s.num_nodes;
+    double all = 0.0;
+    for (int l = 0; l < L; l++) {
+        double e = 0.0;
+        for (size_t c = 0; c < held.size(); c++) {
+            double k = 0.0;                            // sampled by all nodes of the class
+            for (const auto& x : s.degrees[c].cells) k += x.nodes * std::min(x.degree, (double)fanouts[l]);
+            e += held[c] * k / s.degrees[c].nodes;
+        }
+        all += e;
+        for (size_t c = 0; c < held.size() && l + 1 < L; c++) {
+            const auto& k = s.degrees[c];
+            held[c] += (k.nodes - held[c]) * (1.0 - std::exp(-e * k.share / k.nodes));
+        }
+    }
+    return all;
+}
+
+// Whether the unions' workgroups are long enough to lose against the radix sort,
+// which spreads any minibatch over the whole card.  Few minibatches make few
+// workgroups (H K), each of which walks its share of a minibatch's edges alone.
+// In us, fitted to both sides of 240 shapes of 1 to 8 minibatches (within 5 and
+// 7 %): the bitmaps 30 + 36 per hop + 16 per 1024 targets + 11.8 per 1000 edges
+// of a workgroup + 21 per million edges, the radix path 35 + 100 per hop + 5 per
+// 1024 targets + 62 per million edges, and above 32 draws, where its sampler
+// keeps a row's draws in memory, 0.08 times their square and more.  Left to the
+// radix path, bitmaps / radix: 1646 / 520 (regular graph, degree 40, 2^18 nodes,
+// 1 x 4096, [20, 15, 10]), 690 / 430 (R-MAT 2^20, degree 60, the same), 479 / 390
+// (regular, 1 x 1024, [15, 10, 5]); bitmaps: 309 / 386 (R-MAT 2^20, degree 20,
+// 1 x 1024, [20, 15, 10]), 756 / 1213 (degree 60, 1 x 4096, [50, 50]), 317 / 398
+// (regular, 8 x 4096, [10, 5]).
+static bool union_is_serial(const Store& s, const BitmapPlan& p, int H, int B, const int32_t* fanouts, int L) {
+    const double serial = 11.8e-3 / p.K, radix = 41e-6 * H;
+    if (serial <= radix) return false;                 // (the targets alone never decide: 11 us per 1024, at most 4096)
+    double less = 64.0 * L - 0.011 * B;
+    for (int l = 0; l < L; l++)
+        if (fanouts[l] > 32 && s.max_degree > fanouts[l]) less += 0.08 * fanouts[l] * fanouts[l];
+    return (serial - radix) * expected_edges(s, B, fanouts, L) > less;
 }
 
 BitmapPlan bitmap_plan(const Store& s, int H, int B, const int32_t* fanouts, int L, const int64_t* cap) {
@@ -124,7 +198,8 @@ BitmapPlan bitmap_plan(const Store& s, int H, int B, const int32_t* fanouts, int
     // list kernel: 2034 / 1798 at 2^23, 256 x 1024, [25, 10].
     const double wg = p.range_max <= (1 << 17) ? 0.01 : p.range_max <= (1 << 18) ? 0.02 : 0.06;
     p.use = s.join_path == 0 && s.bitmaps && H <= kBmMaxH && B <= kBmMaxB && p.K <= kBmMaxK && p.capE < ((int64_t)1 << 31) &&
-            (int64_t)L * s.nblk <= ((int64_t)1 << 26) && (double)H * p.K * L * wg <= 75.0 * L + 6e-5 * H * edges;
+            (int64_t)L * s.nblk <= ((int64_t)1 << 26) && (double)H * p.K * L * wg <= 75.0 * L + 6e-5 * H * edges &&
+            !union_is_serial(s, p, H, B, fanouts, L);
     return p;
 }
 

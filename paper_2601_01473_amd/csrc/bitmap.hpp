@@ -86,6 +86,10 @@ struct BitmapArgs {
     uint32_t* part;           // pinned: [list_groups][2 + AGNES_MAX_LAYERS] distinct rows, feature blocks, topology blocks
 };
 
+// The store's degree classes, and the edges that a minibatch of B uniform targets
+// is expected to sample in all hops by them.
+void build_degree_classes(Store& s, const std::vector<uint32_t>& indeg, const agnes_csr& csr);
+double expected_edges(const Store& s, int B, const int32_t* fanouts, int L);
 BitmapPlan bitmap_plan(const Store& s, int H, int B, const int32_t* fanouts, int L, const int64_t* cap);
 // What captured launches of the plan depend on, appended to `key`: two stores of
 // one size, one after the other at the same addresses, differ in their node ranges.

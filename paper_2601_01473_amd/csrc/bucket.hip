@@ -129,9 +129,11 @@ static void build_ranges(Store& s, const std::vector<uint32_t>& indeg, double c,
     AGNES_CHECK_HIP(hipMemcpy(s.ranges.ptr, all.data(), all.size() * 4, hipMemcpyHostToDevice));
 }
 
-void build_bucket_levels(Store& s, const int32_t* indices, int64_t n, int64_t e) {
+void build_bucket_levels(Store& s, const agnes_csr& csr) {
+    const int64_t n = csr.num_nodes, e = csr.num_edges;
     std::vector<uint32_t> indeg((size_t)n, 0u);
-    for (int64_t i = 0; i < e; i++) indeg[(size_t)indices[i]]++;
+    for (int64_t i = 0; i < e; i++) indeg[(size_t)csr.indices[i]]++;
+    build_degree_classes(s, indeg, csr);
     const double c = std::max(1.0, (double)e / (4.0 * (double)n));
     double W = 0.0;
     for (int64_t u = 0; u < n; u++) W += (double)indeg[(size_t)u] + c;

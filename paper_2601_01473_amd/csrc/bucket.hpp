@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "../../include/agnes.h"
+
 namespace agnes {
 
 struct Store;
@@ -59,7 +61,7 @@ struct BucketBounds {
 
 // Builds the store's nested bucket levels from the host index array (in-degree
 // weights).
-void build_bucket_levels(Store& s, const int32_t* indices, int64_t n, int64_t e);
+void build_bucket_levels(Store& s, const agnes_csr& csr);
 BucketBounds bucket_bounds(const Store& s, int64_t load, int H);
 // Row stride of the per-minibatch count table for those bounds (sub-buckets
 // rounded up to a multiple of 256).

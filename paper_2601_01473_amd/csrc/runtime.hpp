@@ -240,6 +240,12 @@ struct Store {
     int64_t n_list_blocks = 0;
     int n_list_spans = 0;
     DevBuf list_blocks, list_spans, ranges;
+    // What a minibatch samples is expected from the degrees (expected_edges):
+    // nodes by in-degree, in powers of two, with their share of all edges, and
+    // inside a class by degree, in powers of two, with the mean degree.
+    struct DegreeCell { double nodes, degree; };
+    struct DegreeClass { double nodes, share; std::vector<DegreeCell> cells; };
+    std::vector<DegreeClass> degrees;
     int join_path = 0;                // 1 = node-range buckets, 0 = bitmaps, or radix sort and merge-path join (default)
     int bitmaps = 1;                  // 0 = join path 0 is the radix sort and merge-path join for every shape
     int bucket_cap = 2048;            // entries of a sorted sub-bucket (at most kBucketCap)

@@ -189,7 +189,7 @@ Store* build_store(const agnes_csr* csr, const agnes_features* feat, uint64_t bl
                            s->first_node.as<int32_t>(), s->last_node.as<int32_t>());
     AGNES_CHECK_HIP(hipGetLastError());
     AGNES_CHECK_HIP(hipStreamSynchronize(st));
-    build_bucket_levels(*s, csr->indices, n, e);
+    build_bucket_levels(*s, *csr);
     return s.release();
 }
 

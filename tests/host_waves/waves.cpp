@@ -6,6 +6,8 @@
 // after the other, so a wait for a later one ends the program.
 //
 // waves keys: exit status 0 if plans that launch differently have different keys.
+// waves plan IN: prints the edges that a minibatch is expected to sample, and 1 if the
+// hyperbatch is sampled on bitmaps.
 // waves IN OUT: reads sizes, graph, targets, node ranges and list blocks, runs one
 // hyperbatch and writes its sizes, lists, CSR blocks and statistics.
 #include <stdio.h>
@@ -167,9 +169,38 @@ static bool keys_differ() {
            k != key(8, 4096, 1025, at) && k != key(8, 4096, 1024, at + 4);
 }
 
+// Reads sizes and graph; K node ranges of equal length.
+static int print_plan(const char* path) {
+    using namespace agnes;
+    FILE* in = fopen(path, "rb");
+    if (!in) die("no input");
+    const int64_t* h = read_array<int64_t>(in, 6);
+    const int64_t n = h[0], E = h[1], K = h[5];
+    const int H = (int)h[2], B = (int)h[3], L = (int)h[4];
+    const int32_t* fanouts = read_array<int32_t>(in, L);
+    const int64_t* off = read_array<int64_t>(in, n + 1);
+    const int32_t* adj = read_array<int32_t>(in, E);
+    std::vector<uint32_t> indeg(n, 0u);
+    for (int64_t i = 0; i < E; i++) indeg[adj[i]]++;
+    static Store s;
+    s.num_nodes = n;
+    s.num_edges = E;
+    s.nblk = 1;
+    for (int64_t v = 0; v < n; v++) s.max_degree = std::max(s.max_degree, off[v + 1] - off[v]);
+    for (auto& t : s.range_tab) t = Store::RangeTable{0, (int)K, (int)((n / K + 255) / 256 * 256)};
+    s.n_list_blocks = n / 16 + 1;
+    agnes_csr csr{n, E, AGNES_INT64, off, adj};
+    build_degree_classes(s, indeg, csr);
+    int64_t cap[AGNES_MAX_LAYERS + 1] = {B};
+    for (int l = 0; l < L; l++) cap[l + 1] = std::min<int64_t>(cap[l] * (1 + fanouts[l]), std::max<int64_t>(n, B));
+    printf("%.1f %d\n", expected_edges(s, B, fanouts, L), (int)bitmap_plan(s, H, B, fanouts, L, cap).use);
+    return 0;
+}
+
 int main(int argc, char** argv) {
     using namespace agnes;
     if (argc == 2) return keys_differ() ? 0 : 1;
+    if (argv[1] == std::string("plan")) return print_plan(argv[2]);
     FILE* in = fopen(argv[1], "rb");
     if (!in) die("no input");
     const int64_t* h = read_array<int64_t>(in, 12);

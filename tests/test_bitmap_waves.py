@@ -62,12 +62,54 @@ def waves(tmp_path_factory):
         assert at[0] == len(data)
         return out
 
-    run.exe, run.env = str(exe), env
+    def plan(off, idx, H, B, fan, K=33):
+        with open(d / "in", "wb") as f:
+            for x, t in (([len(off) - 1, len(idx), H, B, len(fan), K], np.int64), (fan, np.int32), (off, np.int64),
+                         (idx, np.int32)):
+                np.asarray(x, t).tofile(f)
+        r = subprocess.run([str(exe), "plan", str(d / "in")], capture_output=True, text=True, env=env, check=True)
+        return float(r.stdout.split()[0]), r.stdout.split()[1] == "1"
+
+    run.exe, run.env, run.plan = str(exe), env, plan
     return run
 
 
 def test_stores_cut_differently_have_different_launch_keys(waves):
     assert subprocess.run([waves.exe, "keys"], env=waves.env).returncode == 0
+
+
+def regular_graph(n, deg, seed):
+    idx = np.random.default_rng(seed).integers(0, n, (n, deg))
+    return np.arange(n + 1, dtype=np.int64) * deg, np.sort(idx, axis=1).astype(np.int32).ravel()
+
+
+@pytest.mark.parametrize("B,fan", [(100, [10, 5]), (1000, [15, 10]), (1000, [20, 15, 10]), (4000, [50]), (50, [3, 0, 3])])
+def test_expected_edges(waves, B, fan):
+    """Within a fifth of what minibatches sample: nodes are taken to be alike inside a
+    power of two of degree and in-degree, and a class's sampled nodes to be spread evenly."""
+    rng = np.random.default_rng(51)
+    n = 20000
+    for off, idx in (regular_graph(n, 24, 52), random_graph(2000, 12, 53, hubs=5, hub_deg=900, multi=True),
+                     (None, None)):
+        if off is None:                                       # in-degrees and degrees skewed alike
+            w = 1.0 / (1.0 + np.arange(n)) ** 0.7
+            deg = np.minimum(rng.poisson(20 * n * w / w.sum()), 3000)
+            off = np.concatenate([[0], np.cumsum(deg)])
+            idx = rng.choice(n, off[-1], p=w / w.sum()).astype(np.int32)
+        b, nn = min(B, len(off) - 1), len(off) - 1
+        o = oracle.Oracle(off, idx)
+        real = np.mean([sum(c.size for c in o.minibatch(t, fan, 3, j).col)
+                        for j, t in enumerate(np.stack([rng.permutation(nn)[:b] for _ in range(4)]).astype(np.int32))])
+        assert abs(waves.plan(off, idx, 1, b, fan)[0] - real) <= 0.2 * real
+
+
+def test_few_large_minibatches_are_left_to_the_radix_path(waves):
+    """One workgroup per range walks its share of a minibatch's edges alone."""
+    off, idx = regular_graph(1 << 16, 40, 54)
+    use = lambda *a: waves.plan(off, idx, *a)[1]              # noqa: E731
+    assert not use(1, 4096, [20, 15, 10]) and not use(2, 4096, [50, 50]) and not use(1, 4096, [25, 20])
+    assert use(16, 4096, [20, 15, 10]) and use(1, 256, [15, 10]) and use(8, 1024, [10, 5])
+    assert use(1, 700, [39, 39]) and not use(1, 700, [40, 40])    # its sampler is slow above 32 draws of more neighbours
 
 
 def check(waves, off, idx, targets, fan, bounds, seed=3, mb=2, rpb=16, e_blk_log2=5):

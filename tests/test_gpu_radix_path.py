@@ -1,10 +1,12 @@
 """The radix sort and merge-path join on small shapes, which bitmaps serve by
 default: the parity, replay, stream, allocator and staged-tier tests once more on
 stores built with AGNES_RADIX_JOIN=1."""
+import numpy as np
 import pytest
 import torch
 
 from tests.graphs import distinct_targets, features, random_graph
+from tests.test_gpu_bitmaps import check, draw_targets
 from tests.test_gpu_parity import (  # noqa: F401
     agnes, test_argument_limits_are_rejected_and_store_stays_usable, test_determinism_reuse_and_grouping,
     test_eight_hops, test_fanout_register_paths, test_finish_on_other_stream_and_errors,
@@ -47,3 +49,30 @@ def test_the_switch_selects_the_path(agnes, monkeypatch):
         agnes.agnes_set_device_allocator(None, None)
     torch.cuda.synchronize()
     assert asked["0"][0] == asked["0"][1] != asked["1"][0]
+
+
+@pytest.mark.parametrize("H,B,fan,left", [(1, 4096, [20, 15, 10], True), (2, 4096, [50, 50], True),
+                                          (1, 4096, [10, 5], False), (16, 1024, [20, 15, 10], False)])
+def test_few_large_minibatches_are_left_to_it(agnes, monkeypatch, H, B, fan, left):
+    """By default, too: they ask for the radix path's buffers, with the oracle's results."""
+    n = 1 << 16
+    off = np.arange(n + 1, dtype=np.int64) * 40
+    idx = np.sort(np.random.default_rng(3).integers(0, n, (n, 40)), axis=1).astype(np.int32).ravel()
+    t = draw_targets(n, H, B, 4)
+    state = {"calls": 0, "fail_at": -1}
+    asked = []
+    agnes.agnes_set_device_allocator(*_failing_allocator(agnes, state))
+    try:
+        for switch in ("0", "1"):
+            monkeypatch.setenv("AGNES_RADIX_JOIN", switch)
+            store = agnes.Store(off, idx, features(n, 1, 1), 4096)
+            state["calls"] = 0
+            b = store.prepare(t, fan, seed=1)
+            asked.append(state["calls"])
+            b.close()
+            store.close()
+    finally:
+        agnes.agnes_set_device_allocator(None, None)
+    assert (asked[0] == asked[1]) == left
+    monkeypatch.setenv("AGNES_RADIX_JOIN", "0")
+    check(agnes, off, idx, t, fan)
