@@ -1,7 +1,7 @@
 """GPU parity of the sampling phase on per-minibatch bitmaps, at the sizes where
 its kernels change course: mask words of the list (32 and 64 minibatches), the
-targets' sort (1024, 2048 and 4096 targets), the sampler's fanout bounds and its
-wave-per-row form, chunks and runs beyond what one round locates, held and new
+targets' placement (a workgroup for every 256 of them), the sampler's fanout bounds
+and its wave-per-row form, chunks and runs beyond what one round locates, held and new
 nodes beyond what LDS lists at once, list blocks of many entries, feature blocks
 that span list blocks, node counts around a block and a range, and the first
 shapes on either side of the limits where the radix sort takes over.  Every
@@ -88,10 +88,15 @@ def test_node_counts(agnes, n):
     check(agnes, off, idx, draw_targets(n, 3, min(n, 300), n), [6, 4], dim=5, block=32)
 
 
-@pytest.mark.parametrize("n", [(1 << 22) + 5, (1 << 24) + 1])
+@pytest.mark.parametrize("n", [(1 << 23) + 5, (1 << 24) + 1, (1 << 25) + 3])
 def test_long_ranges(agnes, n):
-    """Ranges of more than 2^17 nodes: 512 threads per workgroup."""
-    off, idx = skewed_graph(n, 1, 4)
+    """Ranges of more than 2^17 nodes: 512 threads, and above 2^25 nodes more than
+    64 KiB of LDS for the bits.  A range ends at its share of the weight, a 32nd
+    or more (here even, so about as many nodes), or at the longest length, 2^18
+    or 2^19 nodes: whichever comes first makes it long enough."""
+    longest, need = (1 << 18, 1 << 17) if n <= 1 << 25 else (1 << 19, (65536 // 36) << 8)
+    assert min(0.97 * n / 32, longest - 512) > need
+    off, idx = skewed_graph(n, 1, 4, heavy=0.0)
     check(agnes, off, idx, draw_targets(n, 2, 600, 4), [3, 2, 2], dim=1, block=1 << 14)
 
 
@@ -104,12 +109,15 @@ def test_many_held_nodes_in_one_range(agnes):
 
 
 def test_many_new_nodes_in_one_range(agnes):
-    """Neighbours that all fall into one 6000-node part of a large graph."""
-    n = 1 << 17
-    rng = np.random.default_rng(6)
-    off = np.arange(n + 1, dtype=np.int64) * 12
-    idx = np.sort(60000 + rng.integers(0, 500, size=(n, 12)) + 500 * np.arange(12), axis=1).astype(np.int32).ravel()
-    check(agnes, off, idx, draw_targets(n, 3, 1500, 6), [10, 9])
+    """More new nodes in one range than k_bm_union lists at a time (2048): even
+    weights make at most 33 ranges, so more than 33 x 2048 new nodes of a hop put
+    more than 2048 into one of them, and more than 66 x 2048 call for a third window."""
+    n, fan = 1 << 18, [15, 10]
+    off, idx = skewed_graph(n, 20, 6, heavy=0.0)
+    targets = draw_targets(n, 8, 4096, 6)         # (fewer would be left to the radix path)
+    for m in oracle.Oracle(off, idx).hyperbatch(targets, fan, 11, 3):
+        assert np.diff(m.layer_sizes).max() > 66 * 2048
+    check(agnes, off, idx, targets, fan)
 
 
 def test_more_chunks_than_one_round_locates(agnes):
