@@ -122,12 +122,16 @@ double expected_edges(const Store& s, int B, const int32_t* fanouts, int L) {
 // (regular, 1 x 1024, [15, 10, 5]); bitmaps: 309 / 386 (R-MAT 2^20, degree 20,
 // 1 x 1024, [20, 15, 10]), 756 / 1213 (degree 60, 1 x 4096, [50, 50]), 317 / 398
 // (regular, 8 x 4096, [10, 5]).
-static bool union_is_serial(const Store& s, const BitmapPlan& p, int H, int B, const int32_t* fanouts, int L) {
+static bool union_is_serial(const Store& s, const BitmapPlan& p, int H, int B, const int32_t* fanouts, int L,
+                            const int64_t* cap) {
     const double serial = 11.8e-3 / p.K, radix = 41e-6 * H;
     if (serial <= radix) return false;                 // (the targets alone never decide: 11 us per 1024, at most 4096)
-    double less = 64.0 * L - 0.011 * B;
-    for (int l = 0; l < L; l++)
+    double less = 64.0 * L - 0.011 * B, most = 0.0;
+    for (int l = 0; l < L; l++) {
         if (fanouts[l] > 32 && s.max_degree > fanouts[l]) less += 0.08 * fanouts[l] * fanouts[l];
+        most += (double)cap[l] * (double)std::min<int64_t>(fanouts[l], s.max_degree);
+    }
+    if ((serial - radix) * most <= less) return false;  // (small ones need no closer look: 1 to 2 us of the call)
     return (serial - radix) * expected_edges(s, B, fanouts, L) > less;
 }
 
@@ -199,7 +203,7 @@ BitmapPlan bitmap_plan(const Store& s, int H, int B, const int32_t* fanouts, int
     const double wg = p.range_max <= (1 << 17) ? 0.01 : p.range_max <= (1 << 18) ? 0.02 : 0.06;
     p.use = s.join_path == 0 && s.bitmaps && H <= kBmMaxH && B <= kBmMaxB && p.K <= kBmMaxK && p.capE < ((int64_t)1 << 31) &&
             (int64_t)L * s.nblk <= ((int64_t)1 << 26) && (double)H * p.K * L * wg <= 75.0 * L + 6e-5 * H * edges &&
-            !union_is_serial(s, p, H, B, fanouts, L);
+            !union_is_serial(s, p, H, B, fanouts, L, cap);
     return p;
 }
 
