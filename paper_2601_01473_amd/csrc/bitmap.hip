@@ -15,7 +15,7 @@
 //                the lower ranges, plus its rank among the set bits.  Emits the
 //                new nodes, the merged (node, local id) list, the row starts of
 //                the next hop, and every edge's column.
-// Two launches per hop instead of 13 to 16, and a sampled neighbour is written
+// Two launches per hop instead of 10 to 16, and a sampled neighbour is written
 // once and read twice, where the radix sort moves it three times.
 //
 // The gather (and the statistics) want the pairs of all minibatches in (node,
@@ -51,7 +51,11 @@ static int xcd_grid(int64_t items, int most) {
 
 // Rows of one sampling chunk at fanout f: their neighbours fit the LDS stage.
 // Above 32 draws a wave takes a row at a time, so a chunk has 16 rows, four per
-// wave (fanout 40, 27 thousand rows: 68 us with 64 rows per chunk).
+// wave.  A whole prepare with 8 / 16 / 32 / 64 rows, in us: 97 / 96 / 102 / 116
+// (2^15 nodes of degree 200, 8 x 1024, fanout 33), 105 / 110 / 121 / 138 (fanout
+// 64), 232 / 203 / 200 / 199 (2^19 nodes of degree 60, 64 x 1024, fanout 40),
+// 306 / 280 / 269 / 269 (16 x 1024, [7, 40]).  Alone off that line: fanout 256 of
+// 2^15 nodes of degree 200, where 8 rows take 281 and 16, with twice the LDS, 429.
 static int chunk_rows(int f) {
     int r = f <= 32 ? kBlock : 16;
     while (r > 1 && (int64_t)r * f > kBmStage) r >>= 1;
@@ -198,8 +202,14 @@ BitmapPlan bitmap_plan(const Store& s, int H, int B, const int32_t* fanouts, int
     // [5, 5]), 920 / 1031 (2^23, 128 x 1024, [25, 10]), 173 / 204 (2^26, 1 x 64);
     // left to the radix path 1333 / 1103 (2^25, 64 x 1024, [15, 10, 5]),
     // 412 / 289 (2^26, 16 x 1024, [10, 5]), 4627 / 1581 (2^26, 128 x 1024,
-    // [15, 10, 5]).  More than kBmMaxH minibatches take LDS for their masks in the
-    // list kernel: 2034 / 1798 at 2^23, 256 x 1024, [25, 10].
+    // [15, 10, 5]).
+    // Two limits are of the kernels' layout, not of their speed.  kBmMaxH: the list
+    // kernel's masks have up to four words per node.  With eight (256 minibatches of
+    // 64 to 1024 targets) bitmaps took 0.57 to 0.84 of the radix path's time at 2^14
+    // to 2^20 nodes, 0.97 to 1.13 at 2^22 and 2034 / 1798 at 2^23.  kBmMaxB: all of
+    // a minibatch's targets are compared with each other in LDS.  With 8192 of them
+    // 1.53 (2^14 nodes, 64 x 8192, [10]) to 0.87 (2^22, 16 x 8192, [10, 5]), with
+    // 6000 0.67 to 0.79 (32 x 6000, [15, 10]).
     const double wg = p.range_max <= (1 << 17) ? 0.01 : p.range_max <= (1 << 18) ? 0.02 : 0.06;
     p.use = s.join_path == 0 && s.bitmaps && H <= kBmMaxH && B <= kBmMaxB && p.K <= kBmMaxK && p.capE < ((int64_t)1 << 31) &&
             (int64_t)L * s.nblk <= ((int64_t)1 << 26) && (double)H * p.K * L * wg <= 75.0 * L + 6e-5 * H * edges &&

@@ -45,9 +45,9 @@ namespace agnes {
 // share: with pieces of equal length a skewed graph's low ids, and with them a
 // third of the work, would fall to one workgroup.  A list block has at most
 // kBmListNodes nodes and holds whole feature blocks, or a piece of one (where
-// one alone is too long or too heavy).  A range has at most 2^17 nodes (16 KiB of
-// bits), or more where that would make more than 128 ranges, and begins with a
-// list block.
+// one alone is too long or too heavy).  A range begins with a list block and has at
+// most 2^17 nodes (16 KiB of bits); from 2^23 nodes on, where those would be 64
+// ranges, 2^18, and above 2^25 nodes 2^19.
 static void build_ranges(Store& s, const std::vector<uint32_t>& indeg, double c, double W, int64_t n) {
     const double share = W / (double)std::max<int64_t>(1, std::min<int64_t>(16384, n / 16));
     const int64_t rpb = s.rpb;

@@ -1222,8 +1222,11 @@ static void launch_gather_rows_upr(const GatherArgs& a, int groups, int unroll, 
 }
 
 
-// LPR = the power of two lanes that covers a row best (at most a wave).  The
-// list is copied in `chunks` consecutive launches of groups/chunks workgroups.
+// LPR = the least power of two of lanes, from 4 to a wave, that covers a row in
+// one step (32 lanes in two steps for 33 to 63 units of 16 bytes are never faster:
+// per million rows 230 us against 188 with 64 lanes at 33 units, 130 / 125 at 40,
+// 153 / 152 at 48, 364 / 306 at 63; 1.08 million rows of 2^18 nodes).  The list is
+// copied in `chunks` consecutive launches of groups/chunks workgroups.
 template <typename Unit>
 static void launch_gather(const GatherArgs& all, int groups, int unroll, bool nt, int chunks, hipStream_t st) {
     // Rows in flight per lane group when the store leaves it open: 16 for rows
@@ -1936,8 +1939,8 @@ void begin_hyperbatch(const Store& s, Batch& b, const int32_t* targets, bool tar
                        w.sync.as<Ctl>(), (int64_t)H * B);
     AGNES_CHECK_HIP(hipGetLastError());
     // With graph replay, a shape seen twice in a row is captured once and
-    // then replayed: one graph launch instead of 2 launches per hop (about 20
-    // on the radix-sort path).
+    // then replayed: one graph launch instead of 2 launches per hop (on the
+    // radix-sort path 10, 13 or 16: three for every 10 bits of a node id).
     std::vector<uint64_t> key = chain_key(s, b, g, fanouts);
     const bool replay = replay_chain(s, g, fanouts);
     if (replay && !(b.chain && key == b.chain_key) && key == b.last_key)
@@ -2184,7 +2187,7 @@ void wait_batch(Batch& b) {
     AGNES_CHECK_HIP(hipEventSynchronize(b.gathered_at));
     b.stats.sample_ms = b.stats.gather_ms = b.stats.copy_ms = -1.0f;
     if (b.bitmap) {
-        // the partial statistics, copied before the gather
+        // the partial statistics: in pinned memory since the list kernel, which the gather came after
         const SyncLayout y = sync_layout(b.H, b.L, b.rows_max);
         const uint32_t* p = (const uint32_t*)((const char*)b.ws.sync_host.ptr + y.lstat);
         int64_t sum[2 + AGNES_MAX_LAYERS] = {};

@@ -83,7 +83,7 @@ def test_fp16_features(agnes, dims):
 
 
 @pytest.mark.parametrize("dim", [32, 96])
-def test_fp16_own_rows_and_means_in_one_step_of_the_product(agnes, dim):
+def test_fp16_layers_as_wide_as_the_rows(agnes, dim):
     off, idx = random_graph(1500, 9, 5)
     tg = distinct_targets(1500, 3, 50, 3)
     feat = features(1500, dim, 3, np.float16)
