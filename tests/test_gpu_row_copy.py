@@ -32,7 +32,7 @@ def compare(batch, off, idx, feat, t, fan, seed):
         compare_minibatch(got[j], ref[j], oracle.gather(fb, ref[j].nodes), tag=(t.shape, j))
 
 
-@pytest.mark.parametrize("dim", [1, 2, 3, 4, 5, 7, 9, 17, 31, 33, 63, 75, 129, 255, 257, 513, 1025])
+@pytest.mark.parametrize("dim", [1, 2, 3, 4, 5, 7, 8, 9, 17, 31, 33, 63, 75, 129, 255, 257, 513, 1025])
 @pytest.mark.parametrize("unroll", [0, 8, 16])
 def test_row_widths(agnes, dim, unroll):
     log("row width", dim * 4, "unroll", unroll)
