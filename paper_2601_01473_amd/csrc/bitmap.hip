@@ -116,7 +116,7 @@ double expected_edges(const Store& s, int B, const int32_t* fanouts, int L) {
 // Whether the unions' workgroups are long enough to lose against the radix sort,
 // which spreads any minibatch over the whole card.  Few minibatches make few
 // workgroups (H K), each of which walks its share of a minibatch's edges alone.
-// In us, fitted to both sides of 240 shapes of 1 to 8 minibatches (within 5 and
+// In us, fitted to both sides of 160 shapes of 1 to 8 minibatches (within 5 and
 // 7 %): the bitmaps 30 + 36 per hop + 16 per 1024 targets + 11.8 per 1000 edges
 // of a workgroup + 21 per million edges, the radix path 35 + 100 per hop + 5 per
 // 1024 targets + 62 per million edges, and above 32 draws, where its sampler
